@@ -32,6 +32,7 @@
 
 #include "common.h"
 #include "driver.h"
+#include "mlp.h"
 #include "philox.h"
 #include "small.h"
 
@@ -52,7 +53,6 @@ constexpr int kSkip = 18;             // first P_D amplitude among the inputs (r
 constexpr int SA = kInPad + 8;        // LDS row strides (bf16 elements), padded
 constexpr int SH = kHid + 8;          //   against bank conflicts
 constexpr int SO = kOutPad + 8;
-constexpr int kFwdRows = 64;          // rows per tile, inference
 constexpr int kGradRows = 32;         // rows per tile, gradient
 constexpr int kGradSlots = 256;       // workgroups (partial gradients) at most
 constexpr int kMaxPartialRows = 4096;
@@ -177,32 +177,6 @@ __device__ void load_rows(const bf16 *__restrict__ X, int64_t rows, int64_t r0,
     bf16 v = 0;
     if (g < rows && c < kIn) v = X[(idx ? idx[g] : g) * kIn + c];
     dst[i] = v;
-  }
-}
-
-// Inference: out[r][0..10) for all rows; persistent workgroups, weights staged
-// once per workgroup.
-__global__ __launch_bounds__(256) void k_mlp_forward(const float *__restrict__ params,
-                                                     const bf16 *__restrict__ X, int64_t rows,
-                                                     float *__restrict__ out) {
-  __shared__ SWeights w;
-  __shared__ bf16 sX[kFwdRows * SA], sA[kFwdRows * SH], sB[kFwdRows * SH];
-  load_weights(params, w);
-  for (int64_t r0 = (int64_t)blockIdx.x * kFwdRows; r0 < rows;
-       r0 += (int64_t)gridDim.x * kFwdRows) {
-    __syncthreads();
-    load_rows<kFwdRows>(X, rows, r0, nullptr, sX);
-    __syncthreads();
-    layer_fwd<kFwdRows, kInPad, kHid>(sX, SA, w.w1, SA, w.b1, sA, SH);
-    __syncthreads();
-    layer_fwd<kFwdRows, kHid, kHid>(sA, SH, w.w2, SH, w.b2, sB, SH);
-    __syncthreads();
-    layer_fwd<kFwdRows, kHid, kHid>(sB, SH, w.w3, SH, w.b3, sA, SH);
-    __syncthreads();
-    // residual form: the P_D amplitudes (inputs 18..27) plus the network
-    layer_out<kFwdRows>(sA, w, [&](int r, int c, float v) {
-      if (c < kOut && r0 + r < rows) out[(r0 + r) * kOut + c] = v + bf2f(sX[r * SA + kSkip + c]);
-    });
   }
 }
 
@@ -826,12 +800,6 @@ void build_features(const bbl_csr &H, int64_t n_t, int64_t R, double tol, const 
                        stats2, b.PD, F, F32);
   }
   check_launch("features");
-}
-
-void mlp_forward(const float *params, const bf16 *F, int64_t rows, float *out, hipStream_t s) {
-  const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(rows, kFwdRows), 1024));
-  hipLaunchKernelGGL(k_mlp_forward, dim3(grid), dim3(256), 0, s, params, F, rows, out);
-  check_launch("k_mlp_forward");
 }
 
 size_t grad_bytes(int64_t rows) {

@@ -80,6 +80,27 @@ def test_mlp_forward_matches_oracle(torch, bbl, rows):
     assert rel_fro(out, ref) <= 2e-2, rel_fro(out, ref)
 
 
+@pytest.mark.parametrize("rows,shift", [(31, 0), (32, 0), (33, 1), (65, 0), (257, 3), (131137, 0)])
+def test_mlp_forward_tile_edges(torch, bbl, rows, shift):
+    """Row counts around a wave's tile (32 rows, 64 a wave, 256 a workgroup)
+    and past one pass of the grid; `shift` moves the features off every
+    alignment but their own two bytes.  A NaN input row stays NaN and alone."""
+    note("mlp forward tile edges rows=%d shift=%d" % (rows, shift))
+    p, pn = with_output_layer(torch, bbl.mlp_init(3), rows)
+    rng = np.random.default_rng(rows)
+    Fb, F = to_bf16(torch, rng.standard_normal((rows, 28)))
+    bad = rows // 2
+    Fb[bad, 0] = 0x7FC0
+    buf = torch.zeros(rows * 28 + shift, dtype=torch.int16, device="cuda")
+    Fd = buf[shift:].view(rows, 28)
+    Fd.copy_(Fb)
+    out = bbl.mlp_forward(p, Fd).cpu().numpy()
+    keep = np.arange(rows) != bad
+    assert np.all(np.isnan(out[bad])) and np.all(np.isfinite(out[keep]))
+    _, ref16 = op.forward(pn.astype(np.float64), F, act="bf16")
+    assert rel_fro(out[keep], ref16[keep]) <= 2e-3
+
+
 def test_mlp_init_is_he_uniform_and_deterministic(torch, bbl):
     note("mlp init")
     a = bbl.mlp_init(11).cpu().numpy()

@@ -10,21 +10,16 @@
 //             extension of the 20 lowest truncated eigenvectors
 //             (y_ia = (H P)_ia / (theta_a - H_ii) outside the truncation);
 //   network   residual form: the 10 P_D amplitudes of the row plus a
-//             correction by 28 -> 128 -> 128 -> 128 -> 10 with ReLU, BF16
-//             operands on v_mfma_f32_16x16x16bf16_1k, FP32 accumulation, FP32
-//             master weights (output layer initialised to zero, so training
-//             starts from P_D itself); one fused kernel for inference, one for
-//             the gradient;
-//   training  Adam on FP32 master weights; targets are converged eigenvectors
-//             aligned to P_D by orthogonal Procrustes and scaled by sqrt(n);
+//             correction by 28 -> 128 -> 128 -> 128 -> 10 with ReLU (mlp.hip;
+//             output layer initialised to zero, so training starts from P_D
+//             itself);
+//   training  Adam on FP32 master weights (mlp.hip); targets are converged
+//             eigenvectors aligned to P_D by orthogonal Procrustes and scaled
+//             by sqrt(n);
 //   fallback  the plain bootstrap block replaces the learned one when the
 //             learned block has a non-finite entry, a Cholesky pivot of its
 //             Gram matrix below 1e-8 of the largest diagonal entry, or a sum
 //             of k lowest Rayleigh-Ritz values not below the bootstrap's.
-//
-// MFMA layout (16x16x16 bf16, wave64): A[i][k] at lane i + 16 (k / 4),
-// element k % 4; B[k][j] at lane j + 16 (k / 4), element k % 4; D[i][j] at
-// lane j + 16 (i / 4), element i % 4.
 #include <chrono>
 #include <algorithm>
 #include <cmath>
@@ -39,27 +34,14 @@
 namespace bbl {
 namespace {
 
-constexpr int kIn = 28, kInPad = 32, kHid = 128, kOut = 10, kOutPad = 16;
-constexpr int kParams = 38026;
-constexpr int oW1 = 0, oB1 = oW1 + kHid * kIn, oW2 = oB1 + kHid, oB2 = oW2 + kHid * kHid,
-              oW3 = oB2 + kHid, oB3 = oW3 + kHid * kHid, oW4 = oB3 + kHid,
-              oB4 = oW4 + kOut * kHid;
-static_assert(oB4 + kOut == kParams, "parameter layout");
+constexpr int kIn = kMlpIn, kOut = kMlpOut;
 constexpr int kTrunc = 2 * kOut;      // default count of truncated eigenvectors extended one hop
 // truncated eigenvectors of the feature block: opts->feature_vectors, else 2 * 10
 inline int trunc_vectors(const Opts &o) { return o.feature_vectors > 0 ? o.feature_vectors : kTrunc; }
 constexpr int kTruncMax = kMaxBlock;  // the workspaces hold this many
-constexpr int kSkip = 18;             // first P_D amplitude among the inputs (residual form)
-constexpr int SA = kInPad + 8;        // LDS row strides (bf16 elements), padded
-constexpr int SH = kHid + 8;          //   against bank conflicts
-constexpr int SO = kOutPad + 8;
-constexpr int kGradRows = 32;         // rows per tile, gradient
-constexpr int kGradSlots = 256;       // workgroups (partial gradients) at most
 constexpr int kMaxPartialRows = 4096;
 
 typedef uint16_t bf16;
-typedef short s4 __attribute__((ext_vector_type(4)));
-typedef float f4 __attribute__((ext_vector_type(4)));
 
 // float -> bfloat16, round to nearest even; NaN stays a (quiet) NaN
 __device__ inline bf16 f2bf(float f) {
@@ -67,338 +49,6 @@ __device__ inline bf16 f2bf(float f) {
   if ((u & 0x7F800000u) == 0x7F800000u && (u & 0x7FFFFFu)) return (bf16)((u >> 16) | 0x40u);
   u += 0x7FFFu + ((u >> 16) & 1u);
   return (bf16)(u >> 16);
-}
-__device__ inline float bf2f(bf16 h) { return __uint_as_float((uint32_t)h << 16); }
-// ReLU that keeps NaN (so broken weights reach the output and the fallback)
-__device__ inline float relu(float v) { return v > 0.f ? v : (v == v ? 0.f : v); }
-
-__device__ inline f4 mma(s4 a, s4 b, f4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
-}
-__device__ inline s4 ld4(const bf16 *p) { return *reinterpret_cast<const s4 *>(p); }
-__device__ inline s4 ld4s(const bf16 *p, int stride) {
-  s4 r;
-  r[0] = (short)p[0];
-  r[1] = (short)p[stride];
-  r[2] = (short)p[2 * stride];
-  r[3] = (short)p[3 * stride];
-  return r;
-}
-
-// Network weights in LDS as bf16 (zero padded), biases as FP32.
-struct SWeights {
-  bf16 w1[kHid * SA], w2[kHid * SH], w3[kHid * SH], w4[kOutPad * SH];
-  float b1[kHid], b2[kHid], b3[kHid], b4[kOutPad];
-};
-
-__device__ void load_weights(const float *__restrict__ p, SWeights &w) {
-  for (int i = threadIdx.x; i < kHid * SA; i += blockDim.x) {
-    const int r = i / SA, c = i % SA;
-    w.w1[i] = c < kIn ? f2bf(p[oW1 + r * kIn + c]) : (bf16)0;
-  }
-  for (int i = threadIdx.x; i < kHid * SH; i += blockDim.x) {
-    const int r = i / SH, c = i % SH;
-    w.w2[i] = c < kHid ? f2bf(p[oW2 + r * kHid + c]) : (bf16)0;
-    w.w3[i] = c < kHid ? f2bf(p[oW3 + r * kHid + c]) : (bf16)0;
-  }
-  for (int i = threadIdx.x; i < kOutPad * SH; i += blockDim.x) {
-    const int r = i / SH, c = i % SH;
-    w.w4[i] = (r < kOut && c < kHid) ? f2bf(p[oW4 + r * kHid + c]) : (bf16)0;
-  }
-  for (int i = threadIdx.x; i < kHid; i += blockDim.x) {
-    w.b1[i] = p[oB1 + i];
-    w.b2[i] = p[oB2 + i];
-    w.b3[i] = p[oB3 + i];
-  }
-  for (int i = threadIdx.x; i < kOutPad; i += blockDim.x) w.b4[i] = i < kOut ? p[oB4 + i] : 0.f;
-}
-
-// out[r][j] = relu(sum_k in[r][k] W[j][k] + b[j]) for r < TR, j < N, as bf16.
-// 16x16 output tiles are split evenly over the four waves.
-template <int TR, int K, int N>
-__device__ void layer_fwd(const bf16 *in, int sin, const bf16 *W, int sw, const float *bias,
-                          bf16 *out, int sout) {
-  constexpr int RT = TR / 16, T = RT * (N / 16), PER = (T + 3) / 4;
-  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int li = l & 15, lk = 4 * (l >> 4);
-  f4 acc[PER];
-#pragma unroll
-  for (int u = 0; u < PER; ++u) acc[u] = f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int k0 = 0; k0 < K; k0 += 16) {
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      const int t = w * PER + u;
-      if (t < T) {
-        const int rt = t % RT, ct = t / RT;
-        acc[u] = mma(ld4(in + (rt * 16 + li) * sin + k0 + lk),
-                     ld4(W + (ct * 16 + li) * sw + k0 + lk), acc[u]);
-      }
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    const int t = w * PER + u;
-    if (t < T) {
-      const int rt = t % RT, ct = t / RT;
-      const int col = ct * 16 + li;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int row = rt * 16 + lk + q;
-        out[row * sout + col] = f2bf(relu(acc[u][q] + bias[col]));
-      }
-    }
-  }
-}
-
-// Output layer: calls f(row, col, value) for the 16-wide padded output.
-template <int TR, typename F>
-__device__ void layer_out(const bf16 *in, const SWeights &w, F &&f) {
-  constexpr int RT = TR / 16;
-  const int l = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int li = l & 15, lk = 4 * (l >> 4);
-  for (int rt = wv; rt < RT; rt += 4) {
-    f4 acc{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int k0 = 0; k0 < kHid; k0 += 16)
-      acc = mma(ld4(in + (rt * 16 + li) * SH + k0 + lk), ld4(w.w4 + li * SH + k0 + lk), acc);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) f(rt * 16 + lk + q, li, acc[q] + w.b4[li]);
-  }
-}
-
-// Loads rows [r0, r0 + TR) of the features (or the rows idx[r0..]) into LDS.
-template <int TR>
-__device__ void load_rows(const bf16 *__restrict__ X, int64_t rows, int64_t r0,
-                          const int64_t *__restrict__ idx, bf16 *dst) {
-  for (int i = threadIdx.x; i < TR * SA; i += blockDim.x) {
-    const int r = i / SA, c = i % SA;
-    const int64_t g = r0 + r;
-    bf16 v = 0;
-    if (g < rows && c < kIn) v = X[(idx ? idx[g] : g) * kIn + c];
-    dst[i] = v;
-  }
-}
-
-// G[i][j] += sum_r D[r][i] X[r][j] over the TR rows of a tile, i < NI, j < NJ
-// (tiles of 16); accumulated into this workgroup's FP32 partial (row stride
-// ldg, only i < ni, j < nj stored).  Every element has one owning lane, so the
-// read-modify-write needs no atomics and is deterministic.
-template <int TR, int NI, int NJ>
-__device__ void wgrad(const bf16 *D, int sd, const bf16 *X, int sx, float *__restrict__ g,
-                      int ldg, int ni, int nj) {
-  constexpr int IT = NI / 16, T = IT * (NJ / 16), PER = (T + 3) / 4;
-  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int li = l & 15, lk = 4 * (l >> 4);
-  f4 acc[PER];
-#pragma unroll
-  for (int u = 0; u < PER; ++u) acc[u] = f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int k0 = 0; k0 < TR; k0 += 16) {
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      const int t = w * PER + u;
-      if (t < T) {
-        const int it = t % IT, jt = t / IT;
-        acc[u] = mma(ld4s(D + (k0 + lk) * sd + it * 16 + li, sd),
-                     ld4s(X + (k0 + lk) * sx + jt * 16 + li, sx), acc[u]);
-      }
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    const int t = w * PER + u;
-    if (t < T) {
-      const int it = t % IT, jt = t / IT;
-      const int j = jt * 16 + li;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int i = it * 16 + lk + q;
-        if (i < ni && j < nj) g[i * ldg + j] += acc[u][q];
-      }
-    }
-  }
-}
-
-// out[r][j] = (sum_i D[r][i] W[i][j]) * (H[r][j] > 0), i < NI, j < NJ, bf16.
-template <int TR, int NI, int NJ>
-__device__ void backprop(const bf16 *D, int sd, const bf16 *W, int sw, const bf16 *H, int sh,
-                         bf16 *out, int sout) {
-  constexpr int RT = TR / 16, T = RT * (NJ / 16), PER = (T + 3) / 4;
-  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int li = l & 15, lk = 4 * (l >> 4);
-  f4 acc[PER];
-#pragma unroll
-  for (int u = 0; u < PER; ++u) acc[u] = f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int k0 = 0; k0 < NI; k0 += 16) {
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      const int t = w * PER + u;
-      if (t < T) {
-        const int rt = t % RT, jt = t / RT;
-        acc[u] = mma(ld4(D + (rt * 16 + li) * sd + k0 + lk),
-                     ld4s(W + (k0 + lk) * sw + jt * 16 + li, sw), acc[u]);
-      }
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    const int t = w * PER + u;
-    if (t < T) {
-      const int rt = t % RT, jt = t / RT;
-      const int j = jt * 16 + li;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int r = rt * 16 + lk + q;
-        out[r * sout + j] = bf2f(H[r * sh + j]) > 0.f ? f2bf(acc[u][q]) : (bf16)0;
-      }
-    }
-  }
-}
-
-// bias gradient: g[j] += sum_r D[r][j] for j < n (one owning thread per j)
-template <int TR>
-__device__ void bgrad(const bf16 *D, int sd, float *__restrict__ g, int n) {
-  for (int j = threadIdx.x; j < n; j += blockDim.x) {
-    float s = 0.f;
-    for (int r = 0; r < TR; ++r) s += bf2f(D[r * sd + j]);
-    g[j] += s;
-  }
-}
-
-// Gradient of the mean squared error over `rows` rows (features X, or the
-// rows idx[] of X when idx is given) into per-workgroup partials.
-__global__ __launch_bounds__(256) void k_mlp_grad(const float *__restrict__ params,
-                                                  const bf16 *__restrict__ X,
-                                                  const float *__restrict__ T, int64_t rows,
-                                                  const int64_t *__restrict__ idx, float scale,
-                                                  float *__restrict__ partial,
-                                                  double *__restrict__ loss_part) {
-  __shared__ SWeights w;
-  __shared__ bf16 s0[kGradRows * SA], s1[kGradRows * SH], s2[kGradRows * SH], s3[kGradRows * SH];
-  __shared__ bf16 sD[kGradRows * SH], sE[kGradRows * SH];
-  __shared__ double sl[256];
-  float *g = partial + (int64_t)blockIdx.x * kParams;
-  for (int i = threadIdx.x; i < kParams; i += blockDim.x) g[i] = 0.f;
-  load_weights(params, w);
-  double lsum = 0.0;
-  for (int64_t r0 = (int64_t)blockIdx.x * kGradRows; r0 < rows;
-       r0 += (int64_t)gridDim.x * kGradRows) {
-    __syncthreads();
-    load_rows<kGradRows>(X, rows, r0, idx, s0);
-    __syncthreads();
-    layer_fwd<kGradRows, kInPad, kHid>(s0, SA, w.w1, SA, w.b1, s1, SH);
-    __syncthreads();
-    layer_fwd<kGradRows, kHid, kHid>(s1, SH, w.w2, SH, w.b2, s2, SH);
-    __syncthreads();
-    layer_fwd<kGradRows, kHid, kHid>(s2, SH, w.w3, SH, w.b3, s3, SH);
-    __syncthreads();
-    // output layer and d loss / d out = scale * (out - target)
-    layer_out<kGradRows>(s3, w, [&](int r, int c, float v) {
-      const int64_t gr = r0 + r;
-      float d = 0.f;
-      if (c < kOut && gr < rows) {
-        const float diff = v + bf2f(s0[r * SA + kSkip + c]) - T[(idx ? idx[gr] : gr) * kOut + c];
-        lsum += (double)diff * diff;
-        d = scale * diff;
-      }
-      sD[r * SO + c] = f2bf(d);
-    });
-    __syncthreads();
-    wgrad<kGradRows, kOutPad, kHid>(sD, SO, s3, SH, g + oW4, kHid, kOut, kHid);
-    bgrad<kGradRows>(sD, SO, g + oB4, kOut);
-    backprop<kGradRows, kOutPad, kHid>(sD, SO, w.w4, SH, s3, SH, sE, SH);
-    __syncthreads();
-    wgrad<kGradRows, kHid, kHid>(sE, SH, s2, SH, g + oW3, kHid, kHid, kHid);
-    bgrad<kGradRows>(sE, SH, g + oB3, kHid);
-    backprop<kGradRows, kHid, kHid>(sE, SH, w.w3, SH, s2, SH, sD, SH);
-    __syncthreads();
-    wgrad<kGradRows, kHid, kHid>(sD, SH, s1, SH, g + oW2, kHid, kHid, kHid);
-    bgrad<kGradRows>(sD, SH, g + oB2, kHid);
-    backprop<kGradRows, kHid, kHid>(sD, SH, w.w2, SH, s1, SH, sE, SH);
-    __syncthreads();
-    wgrad<kGradRows, kHid, kInPad>(sE, SH, s0, SA, g + oW1, kIn, kHid, kIn);
-    bgrad<kGradRows>(sE, SH, g + oB1, kHid);
-  }
-  sl[threadIdx.x] = lsum;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double s = 0.0;
-    for (int i = 0; i < (int)blockDim.x; ++i) s += sl[i];
-    loss_part[blockIdx.x] = s;
-  }
-}
-
-// grad[p] = sum over slots (fixed order); loss = sum of loss partials / count
-__global__ void k_mlp_grad_reduce(const float *__restrict__ partial, int slots,
-                                  const double *__restrict__ loss_part, double inv_count,
-                                  float *__restrict__ grad, float *__restrict__ loss) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p < kParams) {
-    float s = 0.f;
-    for (int k = 0; k < slots; ++k) s += partial[(int64_t)k * kParams + p];
-    grad[p] = s;
-  }
-  if (p == 0 && loss) {
-    double s = 0.0;
-    for (int k = 0; k < slots; ++k) s += loss_part[k];
-    *loss = (float)(s * inv_count);
-  }
-}
-
-__global__ void k_adam(float *__restrict__ p, float *__restrict__ m, float *__restrict__ v,
-                       const float *__restrict__ g, int64_t count, float lr, float b1, float b2,
-                       float eps, float c1, float c2) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= count) return;
-  const float gi = g[i];
-  const float mi = b1 * m[i] + (1.f - b1) * gi;
-  const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-}
-
-// He-uniform weights (bound sqrt(6 / fan_in)), zero biases; Philox counter
-// (index, 0, 0, 11) under the caller's key.
-__global__ void k_mlp_init(float *__restrict__ p, uint64_t key) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= kParams) return;
-  // hidden layers He-uniform; the output layer (and every bias) zero, so an
-  // untrained network returns the P_D amplitudes unchanged
-  int fan = 0;
-  if (i < oB1) fan = kIn;
-  else if (i >= oW2 && i < oB2) fan = kHid;
-  else if (i >= oW3 && i < oB3) fan = kHid;
-  if (fan == 0) {
-    p[i] = 0.f;
-    return;
-  }
-  U4 c;
-  c.v[0] = (uint32_t)i;
-  c.v[1] = 0;
-  c.v[2] = 0;
-  c.v[3] = 11;
-  const U4 r = philox4x32_10(c, (uint32_t)key, (uint32_t)(key >> 32));
-  const double u = u53(r.v[0], r.v[1]);
-  p[i] = (float)((2.0 * u - 1.0) * sqrt(6.0 / fan));
-}
-
-// Uniform row sample with replacement: idx[r] from Philox counter
-// (r, step, 0, 12), reduced modulo the dataset size.
-__global__ void k_sample(int64_t batch, int64_t total, uint64_t key, uint32_t step,
-                         int64_t *__restrict__ idx) {
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= batch) return;
-  U4 c;
-  c.v[0] = (uint32_t)r;
-  c.v[1] = (uint32_t)((uint64_t)r >> 32);
-  c.v[2] = step;
-  c.v[3] = 12;
-  const U4 o = philox4x32_10(c, (uint32_t)key, (uint32_t)(key >> 32));
-  const uint64_t x = ((uint64_t)o.v[0] << 32) | o.v[1];
-  idx[r] = (int64_t)(x % (uint64_t)total);
 }
 
 // ------------------------------------------------------------- features
@@ -802,33 +452,6 @@ void build_features(const bbl_csr &H, int64_t n_t, int64_t R, double tol, const 
   check_launch("features");
 }
 
-size_t grad_bytes(int64_t rows) {
-  const int slots = (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(rows, kGradRows), kGradSlots));
-  return align_up((size_t)slots * kParams * 4) + align_up((size_t)slots * 8) + 256;
-}
-
-void mlp_grad(const float *params, const bf16 *F, const float *T, int64_t rows,
-              const int64_t *idx, void *ws, float *grad, float *loss, hipStream_t s) {
-  const int slots = (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(rows, kGradRows), kGradSlots));
-  char *base = reinterpret_cast<char *>(align_up(reinterpret_cast<uintptr_t>(ws), 256));
-  float *partial = reinterpret_cast<float *>(base);
-  double *lp = reinterpret_cast<double *>(base + align_up((size_t)slots * kParams * 4));
-  const float scale = (float)(2.0 / ((double)rows * kOut));
-  hipLaunchKernelGGL(k_mlp_grad, dim3(slots), dim3(256), 0, s, params, F, T, rows, idx, scale,
-                     partial, lp);
-  hipLaunchKernelGGL(k_mlp_grad_reduce, dim3(grid_for(kParams)), dim3(256), 0, s, partial, slots,
-                     lp, 1.0 / ((double)rows * kOut), grad, loss);
-  check_launch("k_mlp_grad");
-}
-
-void adam(float *p, float *m, float *v, const float *g, int64_t count, int step, float lr,
-          float b1, float b2, float eps, hipStream_t s) {
-  const float c1 = 1.f - std::pow(b1, (float)step), c2 = 1.f - std::pow(b2, (float)step);
-  hipLaunchKernelGGL(k_adam, dim3(grid_for(count)), dim3(256), 0, s, p, m, v, g, count, lr, b1,
-                     b2, eps, c1, c2);
-  check_launch("k_adam");
-}
-
 }  // namespace
 }  // namespace bbl
 
@@ -916,9 +539,7 @@ int bbl_procrustes_targets(const double *X, const double *P, int64_t n, int32_t 
 int bbl_mlp_init(float *params, uint64_t seed, void *stream) {
   return guarded([&] {
     BBL_REQUIRE(params != nullptr, "params is NULL");
-    hipLaunchKernelGGL(k_mlp_init, dim3(grid_for(kParams)), dim3(256), 0,
-                       static_cast<hipStream_t>(stream), params, seed);
-    check_launch("k_mlp_init");
+    mlp_init(params, seed, static_cast<hipStream_t>(stream));
     return (int)BBL_OK;
   });
 }
@@ -935,7 +556,7 @@ int bbl_mlp_forward(const float *params, const uint16_t *feats, int64_t rows, fl
 
 size_t bbl_mlp_grad_workspace_size(int64_t rows) {
   if (rows < 1) return 0;
-  return grad_bytes(rows);
+  return mlp_grad_bytes(rows);
 }
 
 int bbl_mlp_grad(const float *params, const uint16_t *feats, const float *targets, int64_t rows,
@@ -943,9 +564,8 @@ int bbl_mlp_grad(const float *params, const uint16_t *feats, const float *target
   return guarded([&] {
     BBL_REQUIRE(params && feats && targets && ws && grad, "NULL argument");
     BBL_REQUIRE(rows >= 1, "rows must be >= 1");
-    if (ws_bytes < grad_bytes(rows)) throw Error{BBL_E_NOMEM, "gradient workspace too small"};
-    mlp_grad(params, feats, targets, rows, nullptr, ws, grad, loss,
-             static_cast<hipStream_t>(stream));
+    if (ws_bytes < mlp_grad_bytes(rows)) throw Error{BBL_E_NOMEM, "gradient workspace too small"};
+    mlp_grad(params, feats, targets, rows, ws, grad, loss, static_cast<hipStream_t>(stream));
     return (int)BBL_OK;
   });
 }
@@ -955,15 +575,15 @@ int bbl_adam_step(float *params, float *m, float *v, const float *grad, int64_t 
   return guarded([&] {
     BBL_REQUIRE(params && m && v && grad, "NULL argument");
     BBL_REQUIRE(count >= 1 && step >= 1, "count and step must be >= 1");
-    adam(params, m, v, grad, count, step, lr, beta1, beta2, eps,
-         static_cast<hipStream_t>(stream));
+    mlp_adam(params, m, v, grad, count, step, lr, beta1, beta2, eps,
+             static_cast<hipStream_t>(stream));
     return (int)BBL_OK;
   });
 }
 
 size_t bbl_mlp_train_workspace_size(int64_t batch) {
   if (batch < 1) return 0;
-  return grad_bytes(batch) + align_up((size_t)batch * 8) + align_up((size_t)kParams * 4) + 512;
+  return mlp_train_bytes(batch);
 }
 
 int bbl_mlp_train_step(float *params, float *adam_m, float *adam_v, int32_t step, float lr,
@@ -976,14 +596,8 @@ int bbl_mlp_train_step(float *params, float *adam_m, float *adam_v, int32_t step
     BBL_REQUIRE(dataset_rows >= 1 && batch >= 1 && step >= 1, "bad sizes");
     if (ws_bytes < bbl_mlp_train_workspace_size(batch))
       throw Error{BBL_E_NOMEM, "training workspace too small"};
-    char *base = reinterpret_cast<char *>(align_up(reinterpret_cast<uintptr_t>(ws), 256));
-    int64_t *idx = reinterpret_cast<int64_t *>(base);
-    float *grad = reinterpret_cast<float *>(base + align_up((size_t)batch * 8));
-    char *gws = base + align_up((size_t)batch * 8) + align_up((size_t)kParams * 4);
-    hipLaunchKernelGGL(k_sample, dim3(grid_for(batch)), dim3(256), 0, s, batch, dataset_rows,
-                       sample_key, (uint32_t)step, idx);
-    mlp_grad(params, feats, targets, batch, idx, gws, grad, loss, s);
-    adam(params, adam_m, adam_v, grad, kParams, step, lr, 0.9f, 0.999f, 1e-8f, s);
+    mlp_train_step(params, adam_m, adam_v, step, lr, feats, targets, dataset_rows, batch,
+                   sample_key, ws, loss, s);
     return (int)BBL_OK;
   });
 }

@@ -166,6 +166,70 @@ def test_mlp_gradient_matches_fp64_network(torch, bbl):
     assert max(errs) <= 2e-2, errs
 
 
+@pytest.mark.parametrize("rows", [128, 129, 1025])
+def test_mlp_gradient_tile_edges(torch, bbl, rows):
+    """Row counts around a workgroup's 128 rows, off every alignment but the
+    features' two bytes; the same bars as above."""
+    note("mlp gradient tile edges rows=%d" % rows)
+    p, pn = with_output_layer(torch, bbl.mlp_init(5), rows)
+    rng = np.random.default_rng(rows)
+    Fb, F = to_bf16(torch, rng.standard_normal((rows, 28)))
+    Fd = torch.zeros(rows * 28 + 1, dtype=torch.int16, device="cuda")[1:].view(rows, 28)
+    Fd.copy_(Fb)
+    T = rng.standard_normal((rows, 10)).astype(np.float32)
+    g, loss = bbl.mlp_grad(p, Fd, torch.from_numpy(T).cuda())
+    lref, gref = op.loss_and_grad(pn.astype(np.float64), F, T.astype(np.float64), act="bf16")
+    assert abs(loss.item() - lref) <= 2e-2 * lref
+    gg = g.cpu().numpy().astype(np.float64)
+    o = 0
+    for shape in op.SHAPES:
+        c = int(np.prod(shape))
+        assert rel_fro(gg[o:o + c], gref[o:o + c]) <= 2e-2, shape
+        o += c
+
+
+def test_mlp_gradient_over_several_passes(torch, bbl):
+    """65536 rows are two passes of the largest grid, their halves one each;
+    the loss scale is a power of two apart, so the bfloat16 errors are the same
+    and the gradients differ by float32 summation only: chains of about 500
+    additions, 3e-5 of the sum of magnitudes, which is up to ~30 times the
+    sum."""
+    note("mlp gradient over several passes")
+    p, _ = with_output_layer(torch, bbl.mlp_init(6), 1)
+    rng = np.random.default_rng(2)
+    Fd, _ = to_bf16(torch, rng.standard_normal((65536, 28)))
+    T = torch.from_numpy(rng.standard_normal((65536, 10)).astype(np.float32)).cuda()
+    g, l = bbl.mlp_grad(p, Fd, T)
+    ga, la = bbl.mlp_grad(p, Fd[:32768], T[:32768])
+    gb, lb = bbl.mlp_grad(p, Fd[32768:], T[32768:])
+    ref = 0.5 * (ga.double() + gb.double()).cpu().numpy()
+    assert rel_fro(g.double().cpu().numpy(), ref) <= 1e-3
+    assert abs(l.item() - 0.5 * (la.item() + lb.item())) <= 1e-5 * l.item()
+
+
+def test_mlp_train_step_is_sample_gradient_adam(torch, bbl):
+    """A training step equals the gradient on the rows its Philox counters
+    name, followed by the Adam step."""
+    note("mlp training step")
+    p, _ = with_output_layer(torch, bbl.mlp_init(7), 1)
+    rng = np.random.default_rng(3)
+    total, batch, key = 5000, 333, 0x123456789ABCDEF
+    Fd, _ = to_bf16(torch, rng.standard_normal((total, 28)))
+    T = torch.from_numpy(rng.standard_normal((total, 10)).astype(np.float32)).cuda()
+    idx = []
+    for r in range(batch):
+        o = synthgen.philox4x32_10([r, 0, 1, 12], [key & 0xFFFFFFFF, key >> 32])
+        idx.append(((int(o[0]) << 32) | int(o[1])) % total)
+    idx = torch.tensor(idx, device="cuda")
+    g, l = bbl.mlp_grad(p, Fd[idx].contiguous(), T[idx].contiguous())
+    q, m, v = p.clone(), torch.zeros_like(p), torch.zeros_like(p)
+    bbl.adam_step(q, m, v, g, 1, 1e-3)
+    tr = bbl.MlpTrainer(p, batch, key)
+    loss = tr.step(Fd, T, 1e-3)
+    assert torch.equal(loss, l)
+    assert torch.equal(tr.m, m) and torch.equal(tr.v, v) and torch.equal(tr.params, q)
+
+
 def test_mlp_gradient_is_deterministic(torch, bbl):
     note("mlp gradient determinism")
     p = bbl.mlp_init(8)

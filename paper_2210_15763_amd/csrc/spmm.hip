@@ -3,11 +3,12 @@
 // each matrix element (value + column) is streamed from HBM once per block of
 // vectors; on the GPU the loop over a lives in registers of one lane.
 //
-// Mapping: LPR lanes of a 64-wide wavefront share one row; each lane takes
-// every LPR-th element of the row (coalesced reads of col/val), gathers the
-// whole row of V for that column with vector loads, and accumulates nvec
-// partial sums; a butterfly over the LPR lanes finishes the row.  Rows are
-// independent, no atomics, so results are bitwise reproducible.
+// Mapping: LPR lanes of a 64-wide wavefront share one row; each lane loads
+// every LPR-th element of the row (coalesced reads of col/val), groups of E
+// lanes gather the rows of V for their E columns together, and each lane
+// accumulates nvec / E partial sums; a butterfly over the LPR lanes finishes
+// the row.  Rows are independent, no atomics, so results are bitwise
+// reproducible.
 #include <type_traits>
 
 #include "common.h"
@@ -79,6 +80,87 @@ __device__ __forceinline__ Quad<T> load_quad(const T *__restrict__ p) {
   return q;
 }
 
+// Value of lane (own quad's or pair's first lane) + e, for groups of E lanes.
+template <int E>
+__device__ __forceinline__ int group_lane(int v, int e) {
+  if constexpr (E == 1) return v;
+  if constexpr (E == 2)
+    return e == 0 ? __builtin_amdgcn_mov_dpp(v, 0xA0, 0xF, 0xF, true)   // quad_perm 0,0,2,2
+                  : __builtin_amdgcn_mov_dpp(v, 0xF5, 0xF, 0xF, true);  // quad_perm 1,1,3,3
+  switch (e) {
+    case 0: return __builtin_amdgcn_mov_dpp(v, 0x00, 0xF, 0xF, true);
+    case 1: return __builtin_amdgcn_mov_dpp(v, 0x55, 0xF, 0xF, true);
+    case 2: return __builtin_amdgcn_mov_dpp(v, 0xAA, 0xF, 0xF, true);
+    default: return __builtin_amdgcn_mov_dpp(v, 0xFF, 0xF, 0xF, true);
+  }
+}
+template <int E>
+__device__ __forceinline__ float group_lane(float v, int e) {
+  return __int_as_float(group_lane<E>(__float_as_int(v), e));
+}
+template <int E>
+__device__ __forceinline__ double group_lane(double v, int e) {
+  return __hiloint2double(group_lane<E>(__double2hiint(v), e),
+                          group_lane<E>(__double2loint(v), e));
+}
+
+// Lanes that share one entry's row of V: 16-byte pieces where the row splits
+// evenly (two from 32 bytes on, four from 64).  A gather instruction looks up
+// one cache line per distinct row it touches, so E lanes a row need an E-th of
+// the lookups of one lane that reads the row in E pieces.
+// Narrower rows, and rows that would split into pieces off 8 bytes (10
+// floats: 516 against 487 us, below), keep one lane.
+template <typename XT, int B>
+constexpr int entry_lanes() {
+  constexpr int bytes = (int)sizeof(XT) * B;
+  return bytes >= 64 && B % 4 == 0 ? 4 : bytes >= 32 && bytes % 16 == 0 ? 2 : 1;
+}
+
+// U * LPR entries of a row from offset q on: a lane loads U entries, and every
+// group of E lanes gathers its E entries' rows one after the other, each lane
+// its piece.  All loads are issued before the first product.  FULL: all these
+// entries exist; otherwise lanes past the row's end load nothing and add an
+// exact zero.
+template <typename VT, typename XT, typename AT, int B, int E, int LPR, int U, bool FULL>
+__device__ __forceinline__ void spmm_step(const int32_t *__restrict__ col,
+                                          const VT *__restrict__ val, const XT *__restrict__ X,
+                                          int q, int len, int pc, AT (&acc)[E][B / E]) {
+  constexpr int PB = B / E;
+  int c[U];
+  VT h[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    c[u] = 0;
+    h[u] = VT(0);
+    if (FULL || q + u * LPR < len) {
+      c[u] = col[q + u * LPR];
+      h[u] = val[q + u * LPR];
+    }
+  }
+  XT x[U][E][PB];
+  AT hv[U][E];
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int64_t ce = group_lane<E>(c[u], e);
+      hv[u][e] = (AT)group_lane<E>(h[u], e);
+      if (FULL || q - pc + e + u * LPR < len) {
+        __builtin_memcpy(x[u][e], X + ce * B, sizeof(XT) * PB);
+      } else {
+#pragma unroll
+        for (int a = 0; a < PB; ++a) x[u][e][a] = XT(0);
+      }
+    }
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+#pragma unroll
+      for (int a = 0; a < PB; ++a) acc[e][a] = fma(hv[u][e], (AT)x[u][e][a], acc[e][a]);
+}
+
+// A lane takes whole rows of V (E = 1).
 template <typename VT, typename XT, typename AT, typename YT, int B, int LPR>
 __global__ __launch_bounds__(256) void k_spmm(int64_t n, const int64_t *__restrict__ rp,
                                               const int32_t *__restrict__ col,
@@ -137,6 +219,76 @@ __global__ __launch_bounds__(256) void k_spmm(int64_t n, const int64_t *__restri
         if (a == a0 + sub) v = acc[a];
       if (a0 + sub < B) Y[row * B + a0 + sub] = (YT)v;
     }
+  }
+}
+
+// LPR lanes a row, E of them an entry (entry_lanes).  Bound by the L1's line
+// lookups and misses of the gathers: on n = 2e6, 200 entries a row with every
+// gather an L1 hit the 8-wide float product takes 0.85 ms, on 1000-row
+// sectors 1.7 (1.9 with a lane per entry); n = 4e5, 211 entries a row, us here
+// against a lane per entry: 8 floats 360 / 386, 12 486 / 516, 16 415 / 735; 4
+// doubles 419 / 429, 8 482 / 803, 10 720 / 1012, 16 631 / 1762.  Four steps
+// of 16 entries in flight a row (two of wide rows) beat eight and two, 32 or
+// 64 lanes a row, eight waves a SIMD by a register limit, and streaming
+// (non-temporal) index loads; workgroups of 512 or 1024 contiguous rows, or
+// neighbouring workgroups steered to one CU, changed nothing.
+template <typename VT, typename XT, typename AT, typename YT, int B, int LPR>
+__global__ __launch_bounds__(256) void k_spmm_split(int64_t n, const int64_t *__restrict__ rp,
+                                              const int32_t *__restrict__ col,
+                                              const VT *__restrict__ val,
+                                              const XT *__restrict__ X, YT *__restrict__ Y) {
+  constexpr int RPW = kWave / LPR, E = entry_lanes<XT, B>(), PB = B / E;
+  // registers of the rows in flight: at most 64 a lane
+  constexpr int U = sizeof(XT) * B <= 64 ? 4 : sizeof(XT) * B <= 128 ? 2 : 1;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int sub = lane & (LPR - 1), pc = lane & (E - 1);
+  const int64_t wave_id = xcd_block(blockIdx.x) * (blockDim.x / kWave) + (threadIdx.x / kWave);
+  const int64_t row = wave_id * RPW + lane / LPR;
+  // one sum per entry of a group and piece, as many as a lane per entry keeps:
+  // no longer chains of additions
+  AT part[E][PB];
+#pragma unroll
+  for (int e = 0; e < E; ++e)
+#pragma unroll
+    for (int a = 0; a < PB; ++a) part[e][a] = AT(0);
+  if (row < n) {
+    const int64_t p0 = rp[row];
+    const int len = (int)(rp[row + 1] - p0);
+    const int32_t *cr = col + p0;
+    const VT *vr = val + p0;
+    const XT *Xp = X + pc * PB;
+    int q = 0;
+    for (; q + U * LPR <= len; q += U * LPR)
+      spmm_step<VT, XT, AT, B, E, LPR, U, true>(cr, vr, Xp, q + sub, len, pc, part);
+    while (q < len) {
+      if (U >= 4 && len - q > 2 * LPR) {
+        spmm_step<VT, XT, AT, B, E, LPR, U, false>(cr, vr, Xp, q + sub, len, pc, part);
+        q += U * LPR;
+      } else if (U >= 2 && len - q > LPR) {
+        spmm_step<VT, XT, AT, B, E, LPR, 2, false>(cr, vr, Xp, q + sub, len, pc, part);
+        q += 2 * LPR;
+      } else {
+        spmm_step<VT, XT, AT, B, E, LPR, 1, false>(cr, vr, Xp, q + sub, len, pc, part);
+        q += LPR;
+      }
+    }
+  }
+  AT acc[PB];
+#pragma unroll
+  for (int a = 0; a < PB; ++a) {
+    if constexpr (E == 2) acc[a] = part[0][a] + part[1][a];
+    else acc[a] = (part[0][a] + part[1][a]) + (part[2][a] + part[3][a]);
+  }
+#pragma unroll
+  for (int off = LPR / 2; off >= E; off >>= 1) {
+#pragma unroll
+    for (int a = 0; a < PB; ++a) acc[a] += __shfl_xor(acc[a], off, LPR);
+  }
+  if (row < n && sub < E) {
+    YT y[PB];
+#pragma unroll
+    for (int a = 0; a < PB; ++a) y[a] = (YT)acc[a];
+    __builtin_memcpy(Y + row * B + sub * PB, y, sizeof(YT) * PB);
   }
 }
 
@@ -329,13 +481,16 @@ __global__ __launch_bounds__(256) void k_residual(int64_t n, const int64_t *__re
   }
 }
 
-// Lanes per row.  Measured on MI355X (n = 2e6, ~200 nnz/row, b = 8 FP32):
-// 16 lanes per row with four gathers in flight per lane was the fastest
-// layout; the kernel is bound by the random V-row gathers, not by the CSR
-// stream (which alone reads at ~5.9 TB/s).
+// Lanes per row.  16 with four steps in flight were the fastest on long
+// matrices (n = 2e6, 200 nonzeros a row), 32 from 400 nonzeros a row on.
+// Short matrices leave the chip idle and are bound by the chain of steps of a
+// row, which more lanes shorten: 8 floats wide, 121 nonzeros a row, 16 / 32 /
+// 64 lanes: n = 1000 8.4 / 5.9 / 4.3 us, 3000 10.0 / 6.8 / 5.0, 8000 6.0 / 5.6
+// / 6.4, 20,000 9.4 / 9.5 / 9.9 (41 a row: 5.7 / 6.4 / 7.8).
 int pick_lpr(const bbl_csr &H) {
+  if (H.n <= 4096) return 64;
   const double z = H.n > 0 ? (double)H.nnz / (double)H.n : 0.0;
-  return z < 400.0 ? 16 : 32;
+  return z < 400.0 && H.n > 8192 ? 16 : 32;
 }
 
 template <typename VT, typename XT, typename AT, typename YT, int LPR>
@@ -350,19 +505,28 @@ void spmm_dispatch_b(const bbl_csr &H, const XT *X, YT *Y, int nvec, hipStream_t
     const int64_t grid = ceil_div(ceil_div(nr, rows_per_wg), kXcds) * kXcds;
     const int64_t *rp = H.row_ptr + r0;
     YT *Yc = Y + r0 * nvec;
-#define BBL_SPMM_CASE(BV)                                                                      \
-  case BV:                                                                                     \
-    hipLaunchKernelGGL((k_spmm<VT, XT, AT, YT, BV, LPR>), dim3(grid), dim3(256), 0, s, nr, rp, \
-                       H.col, val, X, Yc);                                                     \
+#define BBL_SPMM_CASE(BV)                                                                       \
+  case BV:                                                                                      \
+    if constexpr (entry_lanes<XT, BV>() > 1)                                                    \
+      hipLaunchKernelGGL((k_spmm_split<VT, XT, AT, YT, BV, LPR>), dim3(grid), dim3(256), 0, s,  \
+                         nr, rp, H.col, val, X, Yc);                                            \
+    else                                                                                        \
+      hipLaunchKernelGGL((k_spmm<VT, XT, AT, YT, BV, LPR>), dim3(grid), dim3(256), 0, s, nr, rp, \
+                         H.col, val, X, Yc);                                                    \
     break;
     switch (nvec) {
       BBL_SPMM_CASE(1)
       BBL_SPMM_CASE(2)
+      BBL_SPMM_CASE(3)
       BBL_SPMM_CASE(4)
+      BBL_SPMM_CASE(5)
+      BBL_SPMM_CASE(6)
       BBL_SPMM_CASE(8)
       BBL_SPMM_CASE(10)
       BBL_SPMM_CASE(12)
       BBL_SPMM_CASE(16)
+      BBL_SPMM_CASE(20)
+      BBL_SPMM_CASE(24)
       BBL_SPMM_CASE(32)
       default:
         hipLaunchKernelGGL((k_spmm_generic<VT, XT, AT, YT, LPR>), dim3(grid), dim3(256), 0, s, nr,

@@ -78,6 +78,43 @@ def test_spmm_matches_oracle_within_dot_product_bound(torch, bbl, nvec, prec):
     assert np.all(np.abs(W - ref) <= bound), np.max(np.abs(W - ref) / bound)
 
 
+@pytest.mark.parametrize("n", [3001, 6001, 20000])
+@pytest.mark.parametrize("nvec,prec", [(4, "f64"), (5, "f32"), (7, "f64"), (8, "f32"), (10, "f64"),
+                                       (12, "f32"), (16, "f32"), (20, "f64"), (24, "f32"),
+                                       (32, "f64")])
+def test_spmm_lane_splits(torch, bbl, n, nvec, prec):
+    """Every split of a row of V over lanes (one, two, four; runtime width) at
+    64, 32 and 16 lanes a matrix row, on rows of 0 to ~600 entries: the same
+    dot-product bound, and a NaN in V reaching exactly the rows that hold its
+    column."""
+    note("spmm lane splits n=%d nvec=%d %s" % (n, nvec, prec))
+    rng = np.random.default_rng(n + nvec)
+    lens = rng.integers(0, 70, n)
+    lens[rng.integers(0, n, 40)] = rng.integers(100, 600, 40)
+    lens[[0, n - 1]] = [0, 65]
+    rows = np.repeat(np.arange(n), lens)
+    key = np.unique(rows * n + rng.integers(0, n, rows.size))
+    rows, col = key // n, (key % n).astype(np.int32)
+    rp = np.searchsorted(rows, np.arange(n + 1)).astype(np.int64)
+    dt = np.float32 if prec == "f32" else np.float64
+    val = rng.standard_normal(col.size).astype(dt)
+    H = synthgen.CSR(n, rp, col, val.astype(np.float64))
+    Hd = bbl.DeviceCSR.from_host(H, "float32" if prec == "f32" else "float64")
+    V = rng.standard_normal((n, nvec)).astype(dt)
+    W = bbl.spmm(Hd, dev(torch, V)).double().cpu().numpy()
+    V64 = V.astype(np.float64)
+    u = U32 if prec == "f32" else U64
+    bound = gamma(np.diff(rp)[:, None] + 2, u) * oracle.spmm_abs(H, V64) + 1e-300
+    assert np.all(np.abs(W - oracle.spmm(H, V64)) <= bound)
+    bad = int(col[rp[n // 2]:][0])
+    V[bad, nvec - 1] = np.nan
+    hit = np.zeros(n, bool)
+    hit[rows[col == bad]] = True
+    W2 = bbl.spmm(Hd, dev(torch, V)).double().cpu().numpy()
+    assert np.array_equal(np.isnan(W2[:, nvec - 1]), hit)
+    assert np.array_equal(W2[:, :nvec - 1], W[:, :nvec - 1])
+
+
 @pytest.mark.parametrize("nvec,block_rows,prec,q,p", [
     (8, 400, "f32", 20, 0.7), (8, 400, "f64", 20, 0.7), (1, 400, "f32", 20, 0.7),
     (4, 333, "f32", 20, 0.7), (10, 400, "f32", 20, 0.7), (16, 400, "f32", 20, 0.7),

@@ -545,6 +545,50 @@ def test_band_eig_matches_dense_eigh(torch, bbl, N, kd, k):
     assert np.max(np.abs(Sg.T @ Sg - np.eye(k))) <= 1e-12
 
 
+@pytest.mark.parametrize("kd", [1, 2, 4, 8, 10, 16])
+@pytest.mark.parametrize("shape", ["kd-1", "kd", "kd+1", "2w", "3w-1", "3w", "3w+kd", "odd", "wide"])
+def test_band_eig_split_edges(torch, bbl, kd, shape):
+    """Sizes around the two-sided factorisation's splits (no rows, one group
+    or several at the bottom, every padding at the top), and sizes whose
+    factors, and then vectors, no longer fit in LDS; the bars of the dense
+    comparison."""
+    import scipy.linalg
+    w = kd + 1
+    N = {"kd-1": kd - 1, "kd": kd, "kd+1": kd + 1, "2w": 2 * w, "3w-1": 3 * w - 1, "3w": 3 * w,
+         "3w+kd": 3 * w + kd, "odd": 7 * w + kd + 3, "wide": 20400 // (kd + 2)}[shape]
+    if N < 1:
+        pytest.skip("no such size")
+    if shape == "wide":
+        N = min(N, 7001)
+    for k in sorted({1, min(N, 5), min(N, 16)}):
+        note("band eig split edges N=%d kd=%d k=%d" % (N, kd, k))
+        rng = np.random.default_rng(100 * N + kd)
+        band = np.zeros((N, kd + 1))
+        for d in range(min(kd, N - 1) + 1):
+            band[d:, d] = rng.standard_normal(N - d) * (3.0 if d == 0 else 1.0)
+        band[:, 0] += np.linspace(-20, 20, N)
+        low = np.zeros((min(kd, N - 1) + 1, N))
+        for d in range(low.shape[0]):
+            low[d, :N - d] = band[d:, d]
+        lam = scipy.linalg.eig_banded(low, lower=True, eigvals_only=True, select="i",
+                                      select_range=(0, k - 1))
+        last = scipy.linalg.eig_banded(low, lower=True, eigvals_only=True, select="i",
+                                       select_range=(N - 1, N - 1))[0]
+        theta, Sg, top = bbl.band_eig(dev(torch, band), N, kd, k)
+        nrm = max(abs(lam[0]), abs(last))
+        np.testing.assert_allclose(theta, lam, rtol=0, atol=1e-12 * nrm)
+        assert abs(top - last) <= 1e-12 * nrm
+        Sg = Sg.cpu().numpy()
+        TS = np.zeros_like(Sg)
+        for d in range(low.shape[0]):
+            v = band[d:, d][:, None]
+            TS[d:] += v * Sg[:N - d]
+            if d:
+                TS[:N - d] += v * Sg[d:]
+        assert np.max(np.linalg.norm(TS - Sg * theta, axis=0)) <= 1e-11 * nrm
+        assert np.max(np.abs(Sg.T @ Sg - np.eye(k))) <= 1e-12
+
+
 @pytest.mark.parametrize("kd", [4, 6])
 def test_band_eig_double_eigenvalues(torch, bbl, kd):
     """T = diag(B, B): every eigenvalue twice.  Inverse iteration at equal

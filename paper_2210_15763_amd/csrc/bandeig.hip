@@ -132,18 +132,6 @@ __global__ __launch_bounds__(64) void k_sturm(const double *__restrict__ Tb, int
 // R[k+i][k+j] -= w_i R[k+j][k]; the same arithmetic as ldl_sweep.
 constexpr int tri(int a, int b) { return a >= b ? a * (a + 1) / 2 + b : b * (b + 1) / 2 + a; }
 
-// 1/d from the hardware reciprocal estimate and two Newton steps
-// r <- r + r (1 - d r): full double precision for the LDL^T multipliers at a
-// third of the dependent instructions of the IEEE division sequence, which
-// sits on the critical path of every row.
-__device__ __forceinline__ double newton_inv(double d) {
-  double r = __builtin_amdgcn_rcp(d);
-  double e = fma(-d, r, 1.0);
-  r = fma(r, e, r);
-  e = fma(-d, r, 1.0);
-  return fma(r, e, r);
-}
-
 // Steps M..KD of one unrolled group of W = KD + 1 rows, slot indices static.
 // STORE: multipliers l_{k+i,k} to L[(k*KD + i-1) * ls] and 1/d to
 // Dinv[k * ls] (a tiny pivot keeps its sign there); otherwise a tiny pivot
@@ -256,13 +244,6 @@ __host__ __device__ inline Split split_rows(int N, int kd) {
   s.m1 = N - kd - s.m2;
   s.pad = (W - s.m1 % W) % W;
   return s;
-}
-
-// orders the LDS accesses of one wave's lanes (the LDS executes a wave's
-// instructions in order; the compiler must not move them across)
-__device__ __forceinline__ void wave_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
 }
 
 // The band rows that enter a sweep's window, staged in LDS by the sweep's own
@@ -897,14 +878,6 @@ __device__ __forceinline__ double lane_value(double v, int lane) {
                           __builtin_amdgcn_readlane(__double2loint(v), lane));
 }
 
-// v of lane s of the lane's own 16 (DPP row_newbcast)
-template <int S>
-__device__ __forceinline__ double row_value(double v) {
-  return __hiloint2double(
-      __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x150 + S, 0xF, 0xF, true),
-      __builtin_amdgcn_mov_dpp(__double2loint(v), 0x150 + S, 0xF, 0xF, true));
-}
-
 // The factorisation sweep of one end by one wave: lane l holds row l (window
 // slot) of the symmetric (KD + 1) x (KD + 1) window, so a row's step is KD fused
 // multiply-adds a lane instead of KD (KD + 1) / 2, with the pivot column's
@@ -1301,81 +1274,10 @@ __global__ __launch_bounds__(256) void k_rr(const double *__restrict__ Tb, int N
 
 typedef double d4 __attribute__((ext_vector_type(4)));
 
-constexpr int kRrMax = 16;      // pairs of k_rr_fast: one 16 x 16 matrix-core tile
+constexpr int kRrMax = kWaveMat;  // pairs of k_rr_fast: one 16 x 16 matrix-core tile
 constexpr int kRrWaves = 16;
 constexpr int kRrStage = 4 * (2 * kMaxBlock + 1) + 4;  // doubles a wave stages (4 band rows)
 static_assert(kRrStage >= 256, "a wave's 16 x 16 partial product fits its stage");
-
-// 1/sqrt(d) from the hardware estimate and two Newton steps, as newton_inv.
-__device__ __forceinline__ double newton_rsqrt(double d) {
-  double r = __builtin_amdgcn_rsq(d);
-  const double h = 0.5 * d;
-  r = fma(r, fma(-h * r, r, 0.5), r);
-  return fma(r, fma(-h * r, r, 0.5), r);
-}
-
-// Row J of the Cholesky factor: lane c holds column c of R in r, 1 / r_cc in dl.
-template <int J>
-__device__ __forceinline__ void chol_rows(const double *G, int k, int c, double (&r)[kRrMax],
-                                          double &dl, bool &bad) {
-  if constexpr (J < kRrMax) {
-    r[J] = 0.0;
-    if (J < k) {
-      double s = G[J * kRrMax + c];
-#pragma unroll
-      for (int m = 0; m < J; ++m) s = fma(-row_value<J>(r[m]), r[m], s);
-      double p = row_value<J>(s);
-      if (!(p > 1e-12 * G[J * kRrMax + J])) {
-        bad = true;
-        p = 1.0;
-      }
-      const double v = newton_rsqrt(p);
-      r[J] = c >= J ? s * v : 0.0;
-      dl = c == J ? v : dl;
-      chol_rows<J + 1>(G, k, c, r, dl, bad);
-    }
-  }
-}
-template <int A, int M>
-__device__ __forceinline__ void inverse_sum(const double (&r)[kRrMax], const double (&x)[kRrMax],
-                                            double &s) {
-  if constexpr (M < kRrMax) {
-    s = fma(-row_value<M>(r[A]), x[M], s);
-    inverse_sum<A, M + 1>(r, x, s);
-  }
-}
-template <int A>
-__device__ __forceinline__ void inverse_rows(int k, int c, const double (&r)[kRrMax], double dl,
-                                             double (&x)[kRrMax]) {
-  if constexpr (A >= 0) {
-    x[A] = 0.0;
-    if (A < k) {
-      double s = A == c ? 1.0 : 0.0;
-      inverse_sum<A, A + 1>(r, x, s);
-      x[A] = A <= c ? s * row_value<A>(dl) : 0.0;
-    }
-    inverse_rows<A - 1>(k, c, r, dl, x);
-  }
-}
-
-// Cholesky factor R of the k x k matrix G (16-wide rows in LDS) by one wave,
-// lane c % 16 holding column c, and R^{-1} (upper, zero below and past k) to
-// Ri.  Returns true when a squared pivot falls below 1e-12 of its diagonal
-// entry.
-__device__ bool wave_chol_inverse(const double *G, int k, double *Ri, int lane) {
-  double r[kRrMax], x[kRrMax], dl = 1.0;
-  const int c = lane & 15;
-  bool bad = false;
-#pragma unroll
-  for (int j = 0; j < kRrMax; ++j) r[j] = 0.0;
-  chol_rows<0>(G, k, c, r, dl, bad);
-  inverse_rows<kRrMax - 1>(k, c, r, dl, x);
-  if (lane < kRrMax) {
-#pragma unroll
-    for (int a = 0; a < kRrMax; ++a) Ri[a * kRrMax + c] = c < k ? x[a] : 0.0;
-  }
-  return bad;
-}
 
 // Jacobi by one wave on the symmetric n x n matrix A (16-wide rows in LDS, n
 // <= 16): each step rotates n / 2 disjoint pairs of a round-robin schedule.
@@ -1538,8 +1440,14 @@ __global__ __launch_bounds__(64 * kRrWaves) void k_rr_fast(
     }
     collect(acc);
     if (wave == 0) {
-      const bool bad = wave_chol_inverse(M0, k, M1, lane);
-      if (lane == 0) sbad = bad ? 1 : 0;
+      // a squared pivot below 1e-12 of its diagonal entry: nearly dependent
+      double r[kWaveMat], x[kWaveMat], pmin;
+      const int bad = wave_chol(M0, kRrMax, k, 1e-12, 0.0, lane, r, x, pmin);
+      if (lane < kRrMax) {
+#pragma unroll
+        for (int a = 0; a < kRrMax; ++a) M1[a * kRrMax + lane] = lane < k ? x[a] : 0.0;
+      }
+      if (lane == 0) sbad = bad;
     }
     __syncthreads();
     if (sbad) {

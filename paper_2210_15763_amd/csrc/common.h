@@ -94,6 +94,9 @@ int launch_gram(int64_t n, const void *X, int xdtype, int bx, int nblk, int64_t 
                 hipStream_t s);
 // out[m][c] = scale * sum_p partial[p][m][c]   (M x ny)
 void launch_reduce(const double *partial, int P, int M, int ny, double *out, hipStream_t s);
+// Sums P partials of MN doubles into the returned count (~sqrt(P)) of them at
+// tmp, behind or apart from the partials (the first stage of launch_reduce).
+int launch_reduce_parts(const double *partial, int P, int MN, double *tmp, hipStream_t s);
 // Yout = beta * Yin + alpha * X C   (C: M x ny float64, Yout type ydtype)
 void launch_update(int64_t n, const void *X, int xdtype, int bx, int nblk, int64_t xstride,
                    const double *C, int ny, double alpha, const void *Yin, int yindtype,
@@ -124,7 +127,9 @@ void launch_update_when(int64_t n, const void *X, int xdtype, int bx, int nblk, 
 // The update above, also leaving the Gram partials of Yout (as stored) in
 // gpart[p][a][c], p < the returned count, for launch_reduce_when(.., ny, ny);
 // returns 0 when this shape has no fused Gram or gcap_doubles is too small
-// (then only the update ran).
+// (then only the update ran).  update_gram_parts: the count it will return for
+// bx = ny = b in 4, 8, 10, 16 (with 16-byte aligned operands).
+int64_t update_gram_parts(int64_t n, int nblk, int b);
 int launch_update_gram_when(int64_t n, const void *X, int xdtype, int bx, int nblk,
                             int64_t xstride, const double *C, int ny, double alpha,
                             const void *Yin, int yindtype, double beta, void *Yout, int youtdtype,

@@ -144,7 +144,7 @@ struct CheckStream {
   hipEvent_t tev[kTimeRing][kPhaseEv] = {};  // timing events, per block instance
   hipEvent_t eig0 = nullptr, eig1 = nullptr;  // around a check's band eigensolve
   hipEvent_t rs0 = nullptr, rs1 = nullptr;    // around a thick restart
-  double *host = nullptr;
+  double *host = nullptr, *host_dev = nullptr;  // pinned; as the device sees it
   static constexpr int kHostDoubles = 2 * kMaxBlock + 16;
   void create() {
     BBL_HIP(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
@@ -159,8 +159,12 @@ struct CheckStream {
     BBL_HIP(hipEventCreate(&rs1));
     BBL_HIP(hipHostMalloc(reinterpret_cast<void **>(&host), kHostDoubles * sizeof(double),
                           hipHostMallocDefault));
+    BBL_HIP(hipHostGetDevicePointer(reinterpret_cast<void **>(&host_dev), host, 0));
   }
   int *iter_flags(int J) { return reinterpret_cast<int *>(host) + kIterFlags + 4 * (J % kRing); }
+  int *iter_flags_dev(int J) {
+    return reinterpret_cast<int *>(host_dev) + kIterFlags + 4 * (J % kRing);
+  }
 };
 
 std::mutex g_pool_mu;
@@ -316,7 +320,7 @@ struct Solver {
   int64_t slot_stride() const { return n * b; }
 
   int max_partials(int M, int ny) const {
-    return gram_max_partials(L.partial_doubles, M, ny);
+    return gram_max_partials(L.partial_doubles - kPartsMax, M, ny);
   }
 
   // C (M x ny) = X^T Y with X = nblk basis-type blocks
@@ -337,6 +341,45 @@ struct Solver {
                                           beta, Yout, BBL_F64, partial, L.partial_doubles, when, s);
     if (P > 0) launch_reduce_when(partial, P, b, b, G, when, s);
     else gram(Yout, BBL_F64, b, 1, 0, Yout, BBL_F64, b, G, when);
+  }
+
+  // The fast path's small steps run fused (launch_step_*) for the block widths
+  // whose update leaves Gram partials.
+  bool fused_steps() const { return b == 4 || b == 8 || b == 10 || b == 16; }
+  // Partials that outlive the next use of `partial`: its last kPartsMax doubles.
+  double *kept_parts() const { return partial + L.partial_doubles - kPartsMax; }
+
+  // Partials of a b x b product as the fused steps take them: as they are when
+  // one workgroup can add them up, else summed to ~sqrt(P) first.
+  Parts parts_of(double *p, int P) {
+    if ((int64_t)P * b * b <= kPartsMax) return Parts{p, P};
+    double *tmp = p + (size_t)P * b * b;
+    return Parts{tmp, launch_reduce_parts(p, P, b * b, tmp, s)};
+  }
+  // V_J^T W
+  Parts gram_parts(const void *Xp, const void *Y) {
+    return parts_of(partial, launch_gram_when(n, Xp, xd, b, 1, 0, Y, xd, b, partial,
+                                              max_partials(b, b), nullptr, s));
+  }
+  // update_gram leaving the partials of G instead of G (keep: past the next
+  // product that uses `partial`)
+  Parts update_parts(const void *Xp, int xdt, int nblk, int64_t xstride, const double *Cm,
+                     double alpha, const void *Yin, int yindt, double beta, double *Yout,
+                     bool keep) {
+    const int64_t want = update_gram_parts(n, nblk, b);
+    const bool direct = keep && (want + want / 8 + 64) * b * b <= kPartsMax;
+    double *p = direct ? kept_parts() : partial;
+    const size_t cap = L.partial_doubles - kPartsMax;
+    int P = launch_update_gram_when(n, Xp, xdt, b, nblk, xstride, Cm, b, alpha, Yin, yindt, beta,
+                                    Yout, BBL_F64, p, direct ? (size_t)kPartsMax : cap, nullptr, s);
+    if (P == 0) {  // no room for the update's partials
+      p = partial;
+      P = launch_gram_when(n, Yout, BBL_F64, b, 1, 0, Yout, BBL_F64, b, partial,
+                           gram_max_partials(cap, b, b), nullptr, s);
+    }
+    if (keep && p == partial)
+      return Parts{kept_parts(), launch_reduce_parts(p, P, b * b, kept_parts(), s)};
+    return parts_of(p, P);
   }
 
   // Full reorthogonalisation of W' (whose Gram G0 is known) against the
@@ -549,7 +592,8 @@ struct Solver {
   // redone on the full path, which decides those branches on the device.
   void iterate(int J, bool fast, const double *hnorm_dev, PhaseTimer &timer, CheckStream &cq,
                Result &R) {
-    if (fast)  // state as of this block's start, restored if it is redone:
+    const bool fused = fast && fused_steps();
+    if (fast && !fused)  // state as of this block's start, restored if it is redone:
       // max |A_jj|, and the sticky breakdown flag (an earlier block may have
       // raised it; the redone block's own QR decides again)
       launch_copy_pair(dres + kHn2Snap + J % kRing, dres + kHn2Slot, ints + kBreakSnap + J % kRing,
@@ -561,14 +605,40 @@ struct Solver {
     timer.mark(ev, 1, s);
     ++R.spmm_calls;
     fire_armed(cq);
-    gram(slot(J), xd, b, 1, 0, W, xd, b, Araw);
-    launch_set_A(Araw, b, J, band, b, J > 0 ? Bstore + (size_t)(J - 1) * b * b : nullptr, C3,
-                 dres + kHn2Slot, s);
+    const double *Bprev = J > 0 ? Bstore + (size_t)(J - 1) * b * b : nullptr;
+    double *BJ = Bstore + (size_t)J * b * b;
     const int nb3 = J > 0 ? 2 : 1;
+    if (fused) {
+      launch_step_A(gram_parts(slot(J), W), b, J, band, b, Bprev, C3, dres + kHn2Slot,
+                    dres + kHn2Snap + J % kRing, breakdown, ints + kBreakSnap + J % kRing, s);
+      const Parts g0 = update_parts(slot(J > 0 ? J - 1 : 0), xd, nb3, slot_stride(), C3, -1.0, W,
+                                    xd, 1.0, Wp, true);
+      timer.mark(ev, 2, s);
+      gram(basis, xd, b, J + 1, slot_stride(), Wp, BBL_F64, b, C);
+      const Parts g1 = update_parts(basis, xd, J + 1, slot_stride(), C, -1.0, Wp, BBL_F64, 1.0, Wp,
+                                    false);
+      launch_step_qr(g0, g1, b, 0.5, o.tau, hnorm_dev, dres + kHn2Slot, C0, QB, RB, mask, flag,
+                     chol_fail, flag2, s);
+      // fault injection (testing): the block after the marked one needs a redo
+      if (o.fault_block > 0 && J == o.fault_block) launch_store_int(flag2, 1, s);
+      timer.mark(ev, 3, s);
+      const Parts o2 = update_parts(Wp, BBL_F64, 1, 0, C0, 1.0, nullptr, BBL_F64, 0.0, Wp, false);
+      launch_step_finish(o2, b, J, RB, Rinv, BJ, breakdown, band, b, o.m_max * b, flag2, chol_fail,
+                         cq.iter_flags_dev(J), s);
+      launch_update(n, Wp, BBL_F64, b, 1, 0, Rinv, b, 1.0, nullptr, BBL_F64, 0.0, slot(J + 1), xd,
+                    s);
+      ++qr_calls;
+      // fault injection (testing): the marked block's QR lost rank
+      if (o.fault_block > 0 && J == o.fault_block - 1) launch_store_int(breakdown, 1, s);
+      timer.mark(ev, 4, s);
+      BBL_HIP(hipEventRecord(cq.fev[J % kRing], s));
+      return;
+    }
+    gram(slot(J), xd, b, 1, 0, W, xd, b, Araw);
+    launch_set_A(Araw, b, J, band, b, Bprev, C3, dres + kHn2Slot, s);
     update_gram(slot(J > 0 ? J - 1 : 0), xd, nb3, slot_stride(), C3, -1.0, W, xd, 1.0, Wp, G0,
                 nullptr);
     timer.mark(ev, 2, s);
-    double *BJ = Bstore + (size_t)J * b * b;
     if (fast) {
       gram(basis, xd, b, J + 1, slot_stride(), Wp, BBL_F64, b, C);
       update_gram(basis, xd, J + 1, slot_stride(), C, -1.0, Wp, BBL_F64, 1.0, Wp, G1, nullptr);

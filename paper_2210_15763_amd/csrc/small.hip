@@ -314,6 +314,138 @@ __global__ void k_set_B(const double *__restrict__ B, int b, int J, double *band
   }
 }
 
+// Sum of P partials of MN entries into out (LDS), by a workgroup of kStep
+// threads: kStep / MN slices of the partials, eight loads in flight a thread,
+// combined in order.  red: kStep doubles.
+constexpr int kStep = 1024;
+__device__ __forceinline__ void wg_sum_parts(Parts a, int MN, double *red, double *out) {
+  const int t = threadIdx.x, G = kStep / MN, e = t % MN, g = t / MN;
+  double v = 0.0;
+  if (g < G) {
+    const double *q = a.p + e;
+    int p = g;
+    double u[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    for (; p + 7 * G < a.P; p += 8 * G) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) u[i] += q[(int64_t)(p + i * G) * MN];
+    }
+#pragma unroll
+    for (int i = 0; i < 7; ++i)
+      if (p + i * G < a.P) u[i] += q[(int64_t)(p + i * G) * MN];
+    v = ((u[0] + u[1]) + (u[2] + u[3])) + ((u[4] + u[5]) + (u[6] + u[7]));
+  }
+  __syncthreads();
+  red[t] = v;
+  __syncthreads();
+  if (t < MN) {
+    double s = 0.0;
+    for (int i = 0; i < G; ++i) s += red[i * MN + t];
+    out[t] = s;
+  }
+  __syncthreads();
+}
+
+__global__ __launch_bounds__(kStep) void k_step_A(Parts A, int b, int J, double *band, int kd,
+                                                  const double *__restrict__ Bprev, double *C3,
+                                                  double *hn2, double *snap_hn2,
+                                                  const int *breakdown, int *snap_brk) {
+  __shared__ double red[kStep], M[kWaveMat * kWaveMat];
+  wg_sum_parts(A, b * b, red, M);
+  const int t = threadIdx.x;
+  if (t == 0) {  // |A_ii| = |v_i^T H v_i| <= ||H||: a lower estimate of the norm
+    double m = *hn2;
+    *snap_hn2 = m;
+    *snap_brk = *breakdown;
+    for (int i = 0; i < b; ++i) m = fmax(m, fabs(M[i * b + i]));
+    *hn2 = m;
+  }
+  const int off = J > 0 ? b : 0;
+  if (t < b * b) {
+    const int r = t / b, c = t % b;
+    const double a = 0.5 * (M[r * b + c] + M[c * b + r]);
+    C3[(off + r) * b + c] = a;
+    if (J > 0) C3[r * b + c] = Bprev[c * b + r];  // (B_{J-1}^T)[r][c]
+    if (c <= r) band[((int64_t)J * b + r) * (kd + 1) + (r - c)] = a;
+  }
+}
+
+__global__ __launch_bounds__(kStep) void k_step_qr(Parts G0, Parts G1, int b, double eta2,
+                                                   double tau, const double *hnorm_ptr,
+                                                   const double *hn2_ptr, double *C0, double *QB,
+                                                   double *RB, int *mask, int *flag, int *fail,
+                                                   int *flag2) {
+  __shared__ double red[kStep], M0[kWaveMat * kWaveMat], M1[kWaveMat * kWaveMat];
+  wg_sum_parts(G0, b * b, red, M0);
+  wg_sum_parts(G1, b * b, red, M1);
+  const int lane = threadIdx.x;
+  if (lane >= 64) return;
+  int need = 0;
+  double dmax = 0.0;
+  for (int i = 0; i < b; ++i) {
+    need |= M1[i * b + i] < eta2 * M0[i * b + i] ? 1 : 0;
+    dmax = fmax(dmax, M1[i * b + i]);
+  }
+  double r[kWaveMat], x[kWaveMat], pmin;
+  wave_chol(M1, b, b, 0.0, 0.0, lane, r, x, pmin);
+  const double hn = fmax(hnorm_ptr ? *hnorm_ptr : 0.0, hn2_ptr ? *hn2_ptr : 0.0);
+  const double scale = tau * fmax(sqrt(fmax(dmax, 0.0)), hn);
+  const int ok = (dmax > 0.0 && pmin > 1e-14 * dmax && pmin > scale * scale) ? 1 : 0;
+  if (lane == 0) {
+    *flag2 = need;
+    *fail = 1 - ok;
+    if (ok) *flag = 0;
+  }
+  if (ok && lane < b) {
+    mask[lane] = 0;
+#pragma unroll
+    for (int j = 0; j < kWaveMat; ++j) {
+      if (j >= b) continue;
+      C0[j * b + lane] = x[j];
+      RB[j * b + lane] = r[j];
+      QB[j * b + lane] = j == lane ? 1.0 : 0.0;
+    }
+  }
+}
+
+__global__ __launch_bounds__(kStep) void k_step_finish(Parts O2, int b, int J,
+                                                       const double *__restrict__ RB, double *Rinv,
+                                                       double *Bout, int *breakdown, double *band,
+                                                       int kd, int nrows_max, const int *flag2,
+                                                       const int *fail, int *host_flags) {
+  __shared__ double red[kStep], M[kWaveMat * kWaveMat], R[kWaveMat * kWaveMat];
+  wg_sum_parts(O2, b * b, red, M);
+  const int lane = threadIdx.x;
+  if (lane >= 64) return;
+  double dmax = 0.0;
+  for (int i = 0; i < b; ++i) dmax = fmax(dmax, M[i * b + i]);
+  double r[kWaveMat], x[kWaveMat], pmin;
+  const int bad = wave_chol(M, b, b, 0.0, 1e-28 * dmax, lane, r, x, pmin);
+  if (lane < b) {
+#pragma unroll
+    for (int j = 0; j < kWaveMat; ++j) {
+      if (j >= b) continue;
+      R[j * b + lane] = r[j];
+      Rinv[j * b + lane] = x[j];
+    }
+  }
+  wave_fence();
+  for (int i = lane; i < b * b; i += 64) {
+    const int rr = i / b, c = i % b;
+    double v = 0.0;
+    for (int m = rr; m <= c; ++m) v += R[rr * b + m] * RB[m * b + c];
+    v = c >= rr ? v : 0.0;
+    Bout[i] = v;
+    const int row = (J + 1) * b + rr, d = b + rr - c;
+    if (row < nrows_max && d >= 1 && d <= kd) band[(int64_t)row * (kd + 1) + d] = v;
+  }
+  if (lane == 0) {
+    if (bad || !(dmax > 0.0)) *breakdown = 1;  // sticky until the solve ends
+    host_flags[0] = *flag2;
+    host_flags[2] = *fail;
+    __threadfence_system();
+  }
+}
+
 // Column statistics of an n x k row-major block: per workgroup partial sum of
 // squares and the first index of the largest |x|.
 __global__ __launch_bounds__(256) void k_colstats(int64_t n, int k, const double *__restrict__ X,
@@ -549,6 +681,30 @@ void launch_reorth_check(const double *G0, const double *G1, int b, double eta2,
   hipLaunchKernelGGL(k_reorth_check, dim3(1), dim3(64), 0, s, G0, G1, b, eta2, outer, flag,
                      counter);
   check_launch("k_reorth_check");
+}
+
+void launch_step_A(Parts A, int b, int J, double *band, int kd, const double *Bprev, double *C3,
+                   double *hn2, double *snap_hn2, const int *breakdown, int *snap_brk,
+                   hipStream_t s) {
+  hipLaunchKernelGGL(k_step_A, dim3(1), dim3(kStep), 0, s, A, b, J, band, kd, Bprev, C3, hn2,
+                     snap_hn2, breakdown, snap_brk);
+  check_launch("k_step_A");
+}
+
+void launch_step_qr(Parts G0, Parts G1, int b, double eta2, double tau, const double *hnorm_ptr,
+                    const double *hn2_ptr, double *C0, double *QB, double *RB, int *mask,
+                    int *flag, int *fail, int *flag2, hipStream_t s) {
+  hipLaunchKernelGGL(k_step_qr, dim3(1), dim3(kStep), 0, s, G0, G1, b, eta2, tau, hnorm_ptr,
+                     hn2_ptr, C0, QB, RB, mask, flag, fail, flag2);
+  check_launch("k_step_qr");
+}
+
+void launch_step_finish(Parts O2, int b, int J, const double *RB, double *Rinv, double *Bout,
+                        int *breakdown, double *band, int kd, int nrows_max, const int *flag2,
+                        const int *fail, int *host_flags, hipStream_t s) {
+  hipLaunchKernelGGL(k_step_finish, dim3(1), dim3(kStep), 0, s, O2, b, J, RB, Rinv, Bout,
+                     breakdown, band, kd, nrows_max, flag2, fail, host_flags);
+  check_launch("k_step_finish");
 }
 
 void launch_svqb_prepare(const double *O, int b, double tau, const double *hnorm_ptr,

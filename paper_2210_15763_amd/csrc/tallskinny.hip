@@ -1483,6 +1483,19 @@ void launch_reduce_when(const double *partial, int P, int M, int ny, double *out
   check_launch("k_reduce");
 }
 
+int launch_reduce_parts(const double *partial, int P, int MN, double *tmp, hipStream_t s) {
+  const int S = std::max(1, std::min(P / 8, (int)std::ceil(std::sqrt((double)P))));
+  hipLaunchKernelGGL(k_reduce1, dim3((MN + 255) / 256, S), dim3(256), 0, s, partial, P, MN, S, tmp,
+                     (const int *)nullptr);
+  check_launch("k_reduce1");
+  return S;
+}
+
+int64_t update_gram_parts(int64_t n, int nblk, int b) {
+  return b == 16 ? std::max<int64_t>(1, std::min<int64_t>(ceil_div(n, 16 * kU16U), kU16Waves))
+                 : update_parts(n, nblk, b);
+}
+
 void launch_reduce(const double *partial, int P, int M, int ny, double *out, hipStream_t s) {
   launch_reduce_when(partial, P, M, ny, out, nullptr, s);
 }

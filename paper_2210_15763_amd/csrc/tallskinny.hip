@@ -36,16 +36,17 @@ __device__ __forceinline__ d4 mfma16(double a, double b, d4 c) {
 template <typename T>
 __device__ __forceinline__ double ld(const T *p) { return (double)*p; }
 
+constexpr int kGramRowsWgs = 2048;        // workgroups of k_gram_rows
+// up to here a gram keeps to 64 row chunks where those already fill the chip:
+// the reduction of the partials then takes one stage instead of two (about
+// 3 us of the 10-20 us of such a gram)
+constexpr int64_t kGramShort = 65536;
 constexpr int kTilesPerWG = 8;   // 16-column tiles of X handled by one gram WG
-#ifndef BBL_GRAM_WAVES
-#define BBL_GRAM_WAVES 1
-#endif
 #ifndef BBL_GRAM_WAVE_TARGET
 #define BBL_GRAM_WAVE_TARGET 6144
 #endif
-// FP64-MFMA gram over 8-wide FP32 blocks: waves per workgroup, and the
-// number of waves (row chunks x column groups) the grid is sized to
-constexpr int kGramWaves = BBL_GRAM_WAVES;
+// FP64-MFMA gram over 8-wide blocks: the number of waves (row chunks x column
+// groups) the grid is sized to
 constexpr int kGramWaveTarget = BBL_GRAM_WAVE_TARGET;
 // most row chunks of the 8- and 10-wide grams: with one or two column groups
 // (up to 16 blocks of 8) the wave target needs 3072-6144 chunks; at 2048 the
@@ -298,7 +299,7 @@ __global__ __launch_bounds__(256) void k_update(int64_t n, const XT *X, int bx,
 // per basis byte, near the FP64 ridge, so the VALU forms (scalar C operands,
 // 256 FMAs per row and block) run far below the HBM rate; these kernels put
 // the four independent 4x4x4 products of one instruction on four groups of
-// four rows (operand layout as in k_gram_mfma8: A[i][k] at lane 16k + 4g + i,
+// four rows (operand layout as in k_gram_quads: A[i][k] at lane 16k + 4g + i,
 // B[k][j] at 16k + 4g + j, D[i][j] at 16i + 4g + j) and read 16-row tiles,
 // four lanes per row, each lane one 4-column quarter (one float4 or two
 // double2): a load instruction reads 16 whole rows, one contiguous run.
@@ -330,7 +331,7 @@ __device__ __forceinline__ void st4(T *p, const double (&v)[4]) {
 // rows t + 4k + g, k = 0..3, and D(q, h)[i][j] = C[4i + q][4j + h].  The four
 // products' sums are added by two lane shuffles at the end.  One wave takes
 // CG blocks over one row chunk, U tiles in flight; workgroup order as in
-// k_gram_mfma8 (the column groups of a row chunk on one XCD).
+// k_gram_quads (the column groups of a row chunk on one XCD).
 template <typename XT, typename YT, int CG, int U>
 __global__ __launch_bounds__(64) void k_gram_mfma16(int64_t n, const XT *__restrict__ X, int nblk,
                                                     int64_t xstride, const YT *__restrict__ Y,
@@ -550,18 +551,17 @@ __device__ __forceinline__ Vec<T, N> vload(const T *p) {
   return r;
 }
 
-// Gram over 8-wide FP32 basis blocks on v_mfma_f64_4x4x4f64 (four independent
-// 4x4x4 products per instruction; operand layout: block g = (l % 16) / 4,
-// A[i][k] at lane 16k + 4g + i, B[k][j] at lane 16k + 4g + j, D[i][j] at lane
-// 16i + 4g + j).  K runs over rows.  Lane (k, g, e) loads ONE float4 of row
-// r0 + k: X columns c0 + 16g + 4e .. +3 (inside one 8-wide block row), so one
-// load instruction reads four whole 128-byte lines (rows r0..r0+3 of eight
-// basis blocks) and no X element is loaded twice.  Its four components feed
-// four MFMA pairs q = 0..3; in pair q, block g computes the 4x4 tiles of X
-// columns c0 + 16g + 4i + q against Y columns 2j and 2j + 1 (lane j = e loads
-// both with one 16-byte load: half the Y load instructions of columns j and
-// 4 + j, 5-9 % faster at 90-181 blocks).  Each wave covers 64*CG columns and
-// keeps U row groups of four in flight.
+// Gram over 4- or 8-wide basis blocks (Y: n x B) on v_mfma_f64_4x4x4f64 (four
+// independent 4x4x4 products: A[i][k] at lane 16k + 4g + i, B[k][j] at lane
+// 16k + 4g + j, D[i][j] at lane 16i + 4g + j).  K runs over rows.  Lane (k, g,
+// e) loads ONE quad of row r0 + k: X columns c0 + 16g + 4e .. +3 (inside one
+// block row), so one load instruction reads whole runs of four rows of the
+// basis blocks and no X element is loaded twice.  Its four components feed
+// four groups of MFMAs q = 0..3; in group q, block g computes the 4x4 tiles of
+// X columns c0 + 16g + 4i + q against Y columns j NY .. + NY, NY = B / 4 (lane
+// j = e loads both of 8 with one 16-byte load: half the Y load instructions of
+// columns j and 4 + j, 5-9 % faster at 90-181 blocks).  Each wave covers 64
+// columns and keeps U row groups of four in flight.
 //
 // Workgroup order: the gy column groups of one row chunk share that chunk of
 // Y, so they are given workgroup ids congruent modulo 8 (the same XCD, whose
@@ -569,87 +569,88 @@ __device__ __forceinline__ Vec<T, N> vload(const T *p) {
 // super-block i / (8 gy) holds row chunks 8 sb .. 8 sb + 7, inside it
 // column group (i % (8 gy)) / 8 and row chunk 8 sb + i % 8.
 //
-// WPG waves per workgroup: the waves of one workgroup take WPG consecutive
-// column groups of the same row chunk (so they read the same rows of Y at
-// about the same time, from the CU's vector cache), gq = ceil(gy / WPG)
-// workgroups per row chunk in the order above.
-template <int CG, int U, int WPG>
-__global__ __launch_bounds__(64 * WPG) void k_gram_mfma8(int64_t n, const float *__restrict__ X,
-                                                         int M, int64_t xstride,
-                                                         const double *__restrict__ Y,
-                                                         int64_t chunk, int gx, int gy,
-                                                         double *__restrict__ partial,
-                                                         const int *__restrict__ when) {
+// WR waves per workgroup split the rows of its chunk and add their sums in LDS,
+// so that short matrices, which need short runs of rows per wave to fill the
+// chip, do not leave a partial for each of them.
+template <typename XT, typename YT, int B, int U, int WR>
+__global__ __launch_bounds__(64 * WR) void k_gram_quads(int64_t n, const XT *__restrict__ X,
+                                                        int M, int64_t xstride,
+                                                        const YT *__restrict__ Y, int64_t chunk,
+                                                        int gx, int gy,
+                                                        double *__restrict__ partial,
+                                                        const int *__restrict__ when) {
+  constexpr int NY = B / 4;
   if (when && *when == 0) return;
-  const int gq = (gy + WPG - 1) / WPG;
-  const int sb = blockIdx.x / (8 * gq), rem = blockIdx.x % (8 * gq);
-  const int cy = (rem / 8) * WPG + (int)(threadIdx.x >> 6), cx = sb * 8 + rem % 8;
-  if (cx >= gx || cy >= gy) return;
-  const int l = threadIdx.x & 63;
+  __shared__ double red[WR > 1 ? WR : 1][WR > 1 ? 4 * NY * 64 : 1];
+  const int sb = blockIdx.x / (8 * gy), rem = blockIdx.x % (8 * gy);
+  const int cy = rem / 8, cx = sb * 8 + rem % 8;
+  if (cx >= gx) return;
+  const int l = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int k = l >> 4, g = (l & 15) >> 2, e = l & 3;
-  const int c00 = cy * (64 * CG);
-  int64_t xo[CG];
-  bool ok[CG];
+  const int col = cy * 64 + 16 * g + 4 * e;  // first of 4 columns
+  const bool ok = col < M;
+  const XT *xp = X + (int64_t)(ok ? col / B : 0) * xstride + col % B;
+  double acc[4][NY];
 #pragma unroll
-  for (int c = 0; c < CG; ++c) {
-    const int col = c00 + 64 * c + 16 * g + 4 * e;  // first of 4 columns
-    ok[c] = col < M;
-    const int blk = col >> 3, a = col & 7;
-    xo[c] = (int64_t)blk * xstride + a;
-  }
-  double acc[CG][4][2];
+  for (int q = 0; q < 4; ++q)
 #pragma unroll
-  for (int c = 0; c < CG; ++c)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) acc[c][q][0] = acc[c][q][1] = 0.0;
-  const int64_t r0 = (int64_t)cx * chunk;
-  const int64_t r1 = min(n, r0 + chunk);
+    for (int t = 0; t < NY; ++t) acc[q][t] = 0.0;
+  const int64_t sub = chunk / WR;  // a multiple of 4 U
+  const int64_t r0 = (int64_t)cx * chunk + wave * sub;
+  const int64_t r1 = min(n, r0 + sub);
   for (int64_t rb = r0; rb < r1; rb += 4 * U) {
-    double y0[U], y1[U];
-    float4 x[U][CG];
+    YT y[U][NY];
+    XT x[U][4];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int64_t r = rb + 4 * u + k;
-      const bool rok = r < r1;
-      const double2 yy = rok ? *reinterpret_cast<const double2 *>(Y + r * 8 + 2 * e)
-                             : make_double2(0.0, 0.0);
-      y0[u] = yy.x;
-      y1[u] = yy.y;
 #pragma unroll
-      for (int c = 0; c < CG; ++c)
-        x[u][c] = (rok && ok[c]) ? *reinterpret_cast<const float4 *>(X + xo[c] + r * 8)
-                                 : make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int t = 0; t < NY; ++t) y[u][t] = YT(0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) x[u][q] = XT(0);
+      if (r < r1) {
+        __builtin_memcpy(y[u], Y + r * B + NY * e, sizeof(YT) * NY);
+        if (ok) __builtin_memcpy(x[u], xp + r * B, sizeof(XT) * 4);
+      }
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int c = 0; c < CG; ++c) {
-        const double xs[4] = {(double)x[u][c].x, (double)x[u][c].y, (double)x[u][c].z,
-                              (double)x[u][c].w};
+      for (int q = 0; q < 4; ++q)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          acc[c][q][0] = __builtin_amdgcn_mfma_f64_4x4x4f64(xs[q], y0[u], acc[c][q][0], 0, 0, 0);
-          acc[c][q][1] = __builtin_amdgcn_mfma_f64_4x4x4f64(xs[q], y1[u], acc[c][q][1], 0, 0, 0);
-        }
+        for (int t = 0; t < NY; ++t)
+          acc[q][t] = __builtin_amdgcn_mfma_f64_4x4x4f64((double)x[u][q], (double)y[u][t],
+                                                         acc[q][t], 0, 0, 0);
+  }
+  if constexpr (WR > 1) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int t = 0; t < NY; ++t) red[wave][(q * NY + t) * 64 + l] = acc[q][t];
+    __syncthreads();
+    if (wave) return;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int t = 0; t < NY; ++t) {
+        double v = 0.0;
+#pragma unroll
+        for (int w = 0; w < WR; ++w) v += red[w][(q * NY + t) * 64 + l];
+        acc[q][t] = v;
       }
   }
   // D lane l = 16i + 4g + j holds tile (g, q) element (i, j): X column
-  // c0 + 16g + 4i + q with i = k (l >> 4), Y columns 2j and 2j + 1, j = e
-  double *out = partial + (int64_t)cx * M * 8;
+  // c0 + 16g + 4i + q with i = k (l >> 4), Y columns NY j .. + NY, j = e
+  double *out = partial + (int64_t)cx * M * B;
 #pragma unroll
-  for (int c = 0; c < CG; ++c)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int m = c00 + 64 * c + 16 * g + 4 * k + q;
-      if (m < M) {
-        *reinterpret_cast<double2 *>(out + (int64_t)m * 8 + 2 * e) =
-            make_double2(acc[c][q][0], acc[c][q][1]);
-      }
-    }
+  for (int q = 0; q < 4; ++q) {
+    const int m = cy * 64 + 16 * g + 4 * k + q;
+    if (m < M) __builtin_memcpy(out + (int64_t)m * B + NY * e, acc[q], sizeof(double) * NY);
+  }
 }
 
 // Gram over 10-wide FP32 basis blocks (Y: n x 10) on v_mfma_f64_4x4x4f64,
-// with the operand layout of k_gram_mfma8.  Each block's 10 columns take 12
+// with the operand layout of k_gram_quads.  Each block's 10 columns take 12
 // padded columns (three quads, the last ending in two zero columns), so no
 // quad of four consecutive columns straddles two blocks: lane (k, g, e) loads
 // padded columns 64 cy + 16 g + 4 e .. +3 of row r0 + k, two float2 runs
@@ -658,7 +659,7 @@ __global__ __launch_bounds__(64 * WPG) void k_gram_mfma8(int64_t n, const float 
 // (lanes e < 2; zeros in the others).  D lane 16i + 4g + j of product (q, t)
 // holds padded X column 64 cy + 16 g + 4 i + q against Y column 2j + t
 // (t < 2) or 8 + j (t = 2, j < 2); padded columns are not stored.  Work
-// split, grid and workgroup order as in k_gram_mfma8.
+// split, grid and workgroup order as in k_gram_quads.
 template <typename YT, int U>
 __global__ __launch_bounds__(64) void k_gram_mfma10(int64_t n, const float *__restrict__ X,
                                                     int nblk, int64_t xstride,
@@ -890,6 +891,112 @@ __global__ __launch_bounds__(64) void k_gram_v(int64_t n, const XT *__restrict__
 #pragma unroll
       for (int j = 0; j < NY; ++j) out[c * NY + j] = acc[c][j];
   }
+}
+
+// Gram of narrow blocks (B = 4 in float32, 4, 8 or 10 in float64) against all
+// of Y's B columns.  A wave reads RG rows of NX x NBW blocks at a time, each
+// lane one 16-byte piece of a block row, so that every load instruction takes
+// whole 128-byte lines whatever the number of blocks, and keeps the products of
+// its 2 or 4 columns with a row of Y in registers; NX blocks a lane share a
+// loaded row of Y.  Four waves of a workgroup interleave over its rows, and
+// their sums and the row groups' are added before the workgroup writes its one
+// partial (partial[p][m][j], p its row chunk), which keeps the count of
+// partials, and with it the reduction, small.  Column groups of a row chunk get
+// workgroup ids congruent mod 8: one XCD, whose L2 then serves their rereads of
+// Y.  Bound by the reads of X and of Y (FP64; with few blocks Y is much of
+// them): n = 2e6, two FP32 blocks of 4 49 us (290 in a kernel with a column
+// group of 64 a wave, mostly empty), 8 FP64 blocks of 8 280 (419) = 4.1 TB/s.
+template <typename XT, int B>
+struct GramRows {
+  static constexpr int CPL = 16 / (int)sizeof(XT);       // columns of a lane's piece
+  static constexpr int LB = B / CPL;                     // pieces of a block row
+  static constexpr int RG = B * sizeof(XT) >= 64 ? 2 : 128 / (B * (int)sizeof(XT));
+  static constexpr int NBW = 64 / RG / LB;               // blocks a wave reads side by side
+  static_assert(B % CPL == 0 && NBW >= 1, "block row of whole pieces");
+};
+template <typename XT, typename YT, int B, int NX>
+__global__ __launch_bounds__(256) void k_gram_rows(int64_t n, const XT *__restrict__ X, int nblk,
+                                                   int64_t xstride, const YT *__restrict__ Y,
+                                                   int64_t chunk, int gx, int gy,
+                                                   double *__restrict__ partial,
+                                                   const int *__restrict__ when) {
+  using G = GramRows<XT, B>;
+  constexpr int CPL = G::CPL, RG = G::RG, NBW = G::NBW, NV = NX * NBW * B * B;
+  constexpr int U = 4 / NX;  // rows in flight: 64 bytes of X a lane
+  if (when && *when == 0) return;
+  __shared__ double red[4][NV];
+  const int id = (int)blockIdx.x, p = id / (8 * gy) * 8 + id % 8, y = id / 8 % gy;
+  if (p >= gx) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int rg = lane / (64 / RG), in = lane % (64 / RG);
+  const int blk = in / G::LB, pc = in % G::LB;
+  const bool active = blk < NBW;
+  const XT *xp[NX];
+#pragma unroll
+  for (int x = 0; x < NX; ++x) {
+    const int bi = (y * NX + x) * NBW + blk;
+    xp[x] = X + (int64_t)(active && bi < nblk ? bi : 0) * xstride + pc * CPL;
+  }
+  double acc[NX][CPL][B];
+#pragma unroll
+  for (int x = 0; x < NX; ++x)
+#pragma unroll
+    for (int c = 0; c < CPL; ++c)
+#pragma unroll
+      for (int j = 0; j < B; ++j) acc[x][c][j] = 0.0;
+  const int64_t r1 = min(n, (int64_t)(p + 1) * chunk);
+  int64_t row = (int64_t)p * chunk + wave * RG;  // first of the wave's RG rows
+  auto products = [&](const XT (&xv)[NX][CPL], const YT (&yv)[B]) {
+#pragma unroll
+    for (int j = 0; j < B; ++j) {
+      const double yj = (double)yv[j];
+#pragma unroll
+      for (int x = 0; x < NX; ++x)
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) acc[x][c][j] = fma((double)xv[x][c], yj, acc[x][c][j]);
+    }
+  };
+  for (; row + (U - 1) * 4 * RG + RG <= r1; row += U * 4 * RG) {
+    XT xv[U][NX][CPL];
+    YT yv[U][B];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t r = row + u * 4 * RG + rg;
+#pragma unroll
+      for (int x = 0; x < NX; ++x) __builtin_memcpy(xv[u][x], xp[x] + r * B, 16);
+      __builtin_memcpy(yv[u], Y + r * B, sizeof(YT) * B);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) products(xv[u], yv[u]);
+  }
+  for (; row < r1; row += 4 * RG) {
+    const int64_t r = row + rg;
+    if (r < r1) {
+      XT xv[NX][CPL];
+      YT yv[B];
+#pragma unroll
+      for (int x = 0; x < NX; ++x) __builtin_memcpy(xv[x], xp[x] + r * B, 16);
+      __builtin_memcpy(yv, Y + r * B, sizeof(YT) * B);
+      products(xv, yv);
+    }
+  }
+#pragma unroll
+  for (int x = 0; x < NX; ++x)
+#pragma unroll
+    for (int c = 0; c < CPL; ++c)
+#pragma unroll
+      for (int j = 0; j < B; ++j) {
+        double v = acc[x][c][j];
+#pragma unroll
+        for (int off = 64 / RG; off < 64; off <<= 1) v += __shfl_xor(v, off, 64);
+        if (rg == 0 && active) red[wave][(x * NBW + blk) * B * B + (pc * CPL + c) * B + j] = v;
+      }
+  __syncthreads();
+  // the group's blocks are neighbours in the partial, too
+  const int base = y * NV, count = min(NV, nblk * B * B - base);
+  double *out = partial + (int64_t)p * nblk * B * B + base;
+  for (int e = threadIdx.x; e < count; e += 256)
+    out[e] = (red[0][e] + red[1][e]) + (red[2][e] + red[3][e]);
 }
 
 // Yout[r][j] = beta*Yin[r][j] + alpha*sum_m X[r][m] C[m][j], X blocks of width
@@ -1190,6 +1297,62 @@ int gram_valu(int64_t n, const XT *X, int bx, int nblk, int64_t xstride, const Y
   return (int)gx;
 }
 
+template <typename XT, typename YT, int B, int NX>
+int gram_rows(int64_t n, const XT *X, int nblk, int64_t xstride, const YT *Y, double *partial,
+              int max_partials, const int *when, hipStream_t s) {
+  using G = GramRows<XT, B>;
+  const int gy = (int)ceil_div(nblk, NX * G::NBW);
+  // about kGramRowsWgs workgroups, of at least two rounds of rows each; where
+  // 64 row chunks already give every CU a workgroup, no more: the partials
+  // then need one stage of reduction
+  int64_t gx = std::max<int64_t>(1, kGramRowsWgs / gy);
+  gx = std::min(gx, ceil_div(n, 8 * 4 * G::RG));
+  if (n <= kGramShort && gy >= 4) gx = std::min<int64_t>(gx, 64);
+  gx = std::max<int64_t>(1, std::min<int64_t>(gx, max_partials));
+  const int64_t chunk = ceil_div(ceil_div(n, gx), 4 * G::RG) * 4 * G::RG;
+  gx = ceil_div(n, chunk);
+  hipLaunchKernelGGL((k_gram_rows<XT, YT, B, NX>), dim3((unsigned)(ceil_div(gx, 8) * 8 * gy)),
+                     dim3(256), 0, s, n, X, nblk, xstride, Y, chunk, (int)gx, gy, partial, when);
+  check_launch("k_gram_rows");
+  return (int)gx;
+}
+
+template <typename XT, typename YT, int B>
+int gram_quads(int64_t n, const XT *X, int nblk, int64_t xstride, const YT *Y, double *partial,
+               int max_partials, const int *when, hipStream_t s) {
+  // 64 basis columns per wave; about 6k one-wave workgroups in all, so that
+  // the whole grid is resident at once (measured at n = 2e6, 8 floats wide: 45,
+  // 90 and 181 blocks run fastest with 1024, 512 and 256 row chunks, 5.1-5.3
+  // TB/s; 20 blocks with 2048 chunks, 4.8 TB/s against 3.6 with 1024)
+  const int M = nblk * B;
+  const int gy = (M + 63) / 64;
+  int64_t gx = std::min<int64_t>(kGramMaxChunks, ceil_div(kGramWaveTarget, gy));
+  // short row counts: shorter row chunks with more rows in flight, so each
+  // wave takes a few load rounds instead of dozens; four waves a workgroup
+  // (FP32 blocks of 8 one: with four, 20,000 rows by 20 blocks took 16.2
+  // instead of 13.1 us; FP64 blocks of 8 took 13.5)
+  constexpr int WR = sizeof(XT) == 4 && B == 8 ? 1 : 4;
+  const bool small = ceil_div(n, 256) < gx;
+  const int U = small ? (sizeof(XT) == 8 ? kGramSmallU / 2 : kGramSmallU) : 2;
+  const int64_t rows = small ? WR * kGramSmallChunk : 256;  // of a workgroup, at least
+  gx = std::max<int64_t>(1, std::min<int64_t>(gx, ceil_div(n, rows)));
+  if (small && WR > 1 && n <= kGramShort) gx = std::min<int64_t>(gx, 64);
+  gx = std::min<int64_t>(gx, std::max(1, max_partials));
+  const int64_t step = 4 * U * (small ? WR : 1);
+  const int64_t chunk = ceil_div(ceil_div(n, gx), step) * step;
+  gx = ceil_div(n, chunk);
+  const unsigned grid = (unsigned)(ceil_div(gx, 8) * 8 * gy);
+  constexpr int US = sizeof(XT) == 8 ? kGramSmallU / 2 : kGramSmallU;
+  if (small)
+    hipLaunchKernelGGL((k_gram_quads<XT, YT, B, US, WR>), dim3(grid), dim3(64 * WR), 0, s, n, X, M,
+                       xstride, Y, chunk, (int)gx, gy, partial, when);
+  else
+    hipLaunchKernelGGL((k_gram_quads<XT, YT, B, 2, 1>), dim3(grid), dim3(64), 0, s, n, X, M,
+                       xstride, Y, chunk, (int)gx, gy, partial, when);
+  check_launch("k_gram_quads");
+  return (int)gx;
+}
+
 template <typename XT, typename YT, int CG, int U>
 int gram_mfma16(int64_t n, const XT *X, int nblk, int64_t xstride, const YT *Y, double *partial,
                 int max_partials, const int *when, hipStream_t s) {
@@ -1258,44 +1421,40 @@ int gram_typed(int64_t n, const XT *X, int bx, int nblk, int64_t xstride, const 
     check_launch("k_gram_mfma10");
     return (int)gx;
   }
-  if (bx == 8 && ny == 8 && f32 && std::is_same<YT, double>::value && nblk >= 2) {
-    // 64 basis columns per one-wave workgroup; about 6k workgroups in all, so
-    // that the whole grid is resident at once (measured on MI355X at n = 2e6:
-    // 45, 90 and 181 blocks run fastest with 1024, 512 and 256 row chunks,
-    // 5.1-5.3 TB/s; 20 blocks with 2048 chunks, 4.8 TB/s against 3.6 with
-    // 1024)
-    constexpr int CG = 1, WPG = kGramWaves;
-    const int gy = (M + 64 * CG - 1) / (64 * CG);
-    int64_t gx = std::min<int64_t>(kGramMaxChunks, ceil_div(kGramWaveTarget, gy));
-    // short row counts: shorter row chunks with more rows in flight, so each
-    // wave takes a few load rounds instead of dozens
-    const bool small = ceil_div(n, 256) < gx;
-    const int U = small ? kGramSmallU : 2;
-    gx = std::max<int64_t>(1, std::min<int64_t>(gx, ceil_div(n, small ? kGramSmallChunk : 256)));
-    gx = std::min<int64_t>(gx, std::max(1, max_partials));
-    int64_t chunk = ceil_div(ceil_div(n, gx), 4 * U) * (4 * U);
-    gx = ceil_div(n, chunk);
-    const int64_t grid = ceil_div(gx, 8) * 8 * ceil_div(gy, WPG);
-    if (small)
-      hipLaunchKernelGGL((k_gram_mfma8<CG, kGramSmallU, WPG>), dim3((unsigned)grid),
-                         dim3(64 * WPG), 0, s, n, (const float *)X, M, xstride,
-                         (const double *)Y, chunk, (int)gx, gy, partial, when);
+  // 4- and 8-wide blocks.  Up to 8 of them k_gram_rows, whose lanes spread over
+  // the rows (k_gram_quads' group of 64 columns would be partly empty: n = 4e5,
+  // 8 FP64 blocks of 8, 57 us against 69 of k_gram_v and 8 FP32 blocks of 4,
+  // 28 against 67), except FP32 blocks of 8, two to a 64-byte line, where
+  // k_gram_quads has 41 us.  More of them k_gram_quads (n = 4e5, 45 blocks:
+  // FP64 by 8 228 us against 271 of k_gram_v, FP32 by 4 79 against 119), but
+  // k_gram_v for FP64 blocks of 4 (20 blocks 52 us against 64, 150 339
+  // against 361).
+  if (ny == bx && nblk >= 2 && (bx == 4 || bx == 8)) {
+    if (!(f32 && bx == 8) && nblk <= 8) {
+      if (bx == 4)
+        return gram_rows<XT, YT, 4, 1>(n, X, nblk, xstride, Y, partial, max_partials, when, s);
+      if constexpr (!f32)
+        return gram_rows<XT, YT, 8, 1>(n, X, nblk, xstride, Y, partial, max_partials, when, s);
+    }
+    if (bx == 8)
+      return gram_quads<XT, YT, 8>(n, X, nblk, xstride, Y, partial, max_partials, when, s);
+    if constexpr (f32)
+      return gram_quads<XT, YT, 4>(n, X, nblk, xstride, Y, partial, max_partials, when, s);
     else
-      hipLaunchKernelGGL((k_gram_mfma8<CG, 2, WPG>), dim3((unsigned)grid), dim3(64 * WPG), 0, s,
-                         n, (const float *)X, M, xstride, (const double *)Y, chunk, (int)gx, gy,
-                         partial, when);
-    check_launch("k_gram_mfma8");
-    return (int)gx;
+      return gram_valu<XT, YT, 4, 2>(n, X, bx, nblk, xstride, Y, partial, max_partials, when, s);
   }
-  if (ny == bx) {
-    switch (bx) {
-      case 4: return gram_valu<XT, YT, 4, f32 ? 4 : 2>(n, X, bx, nblk, xstride, Y, partial, max_partials, when, s);
-      case 8: return gram_valu<XT, YT, 8, f32 ? 4 : 2>(n, X, bx, nblk, xstride, Y, partial, max_partials, when, s);
-      case 10: return gram_valu<XT, YT, 10, 2>(n, X, bx, nblk, xstride, Y, partial, max_partials, when, s);
-      case 16: return gram_valu<XT, YT, 16, 2>(n, X, bx, nblk, xstride, Y, partial, max_partials, when, s);
-      default: break;
+  // 10-wide FP64 blocks: no power of two of lanes divides them, so k_gram_rows
+  // for any number (n = 4e5, 8 / 45 / 150 blocks 95 / 353 / 1070 us against
+  // 117 / 405 / 1134 of k_gram_v)
+  if constexpr (!f32) {
+    if (bx == 10 && ny == 10 && nblk >= 2) {
+      if (nblk <= GramRows<XT, 10>::NBW)
+        return gram_rows<XT, YT, 10, 1>(n, X, nblk, xstride, Y, partial, max_partials, when, s);
+      return gram_rows<XT, YT, 10, 2>(n, X, nblk, xstride, Y, partial, max_partials, when, s);
     }
   }
+  if (ny == bx && bx == 16)  // off 16-byte alignment
+    return gram_valu<XT, YT, 16, 2>(n, X, bx, nblk, xstride, Y, partial, max_partials, when, s);
   const int tiles = (M + 15) / 16;
   const int gy = (tiles + kTilesPerWG - 1) / kTilesPerWG;
   // row chunk: enough workgroups to fill the chip, bounded partial count

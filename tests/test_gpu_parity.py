@@ -480,6 +480,25 @@ def test_gram_at_a_row_count_past_the_short_row_path(torch, bbl, bx):
     assert np.all(np.abs(C.reshape(Cref.shape) - Cref) <= bound)
 
 
+@pytest.mark.parametrize("yf32", [False, True])
+@pytest.mark.parametrize("bx,xf32", [(4, True), (4, False), (8, True), (8, False), (10, False)])
+@pytest.mark.parametrize("nblk", [2, 6, 7, 8, 9, 17])
+def test_gram_of_narrow_blocks_at_its_edges(torch, bbl, bx, xf32, yf32, nblk):
+    """Block counts around a column group (6 or 8 blocks; 17 of 4 are 68
+    columns, of 8 two groups and a bit) and row counts around a row group, a
+    workgroup's chunk and the launch for long matrices, both types of Y."""
+    rng = np.random.default_rng(1000 * bx + nblk)
+    for n in (1, 3, 31, 129, 4097, 70_001) + ((1_600_003,) if nblk == 9 and not yf32 else ()):
+        note("gram edges bx=%d nblk=%d n=%d x32=%s y32=%s" % (bx, nblk, n, xf32, yf32))
+        Xb = rng.standard_normal((nblk, n, bx)).astype(np.float32 if xf32 else np.float64)
+        Y = rng.standard_normal((n, bx)).astype(np.float32 if yf32 else np.float64)
+        C = bbl.gram(dev(torch, Xb), nblk, bx, dev(torch, Y)).cpu().numpy()
+        Xwide = np.concatenate(list(Xb.astype(np.float64)), axis=1)
+        Y = Y.astype(np.float64)
+        bound = 64 * n * U64 * (np.abs(Xwide).T @ np.abs(Y))
+        assert np.all(np.abs(C.reshape(bound.shape) - Xwide.T @ Y) <= bound), n
+
+
 @pytest.mark.parametrize("n", [1, 7, 17, 33])
 def test_sixteen_wide_products_on_tiny_row_counts(torch, bbl, n):
     """The 16-wide matrix-core gram and update on fewer rows than one 16-row

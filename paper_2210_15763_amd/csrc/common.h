@@ -129,7 +129,7 @@ void launch_update_when(int64_t n, const void *X, int xdtype, int bx, int nblk, 
 // returns 0 when this shape has no fused Gram or gcap_doubles is too small
 // (then only the update ran).  update_gram_parts: the count it will return for
 // bx = ny = b in 4, 8, 10, 16 (with 16-byte aligned operands).
-int64_t update_gram_parts(int64_t n, int nblk, int b);
+int64_t update_gram_parts(int64_t n, int nblk, int b, int xdtype);
 int launch_update_gram_when(int64_t n, const void *X, int xdtype, int bx, int nblk,
                             int64_t xstride, const double *C, int ny, double alpha,
                             const void *Yin, int yindtype, double beta, void *Yout, int youtdtype,

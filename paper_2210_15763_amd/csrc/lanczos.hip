@@ -366,7 +366,7 @@ struct Solver {
   Parts update_parts(const void *Xp, int xdt, int nblk, int64_t xstride, const double *Cm,
                      double alpha, const void *Yin, int yindt, double beta, double *Yout,
                      bool keep) {
-    const int64_t want = update_gram_parts(n, nblk, b);
+    const int64_t want = update_gram_parts(n, nblk, b, xdt);
     const bool direct = keep && (want + want / 8 + 64) * b * b <= kPartsMax;
     double *p = direct ? kept_parts() : partial;
     const size_t cap = L.partial_doubles - kPartsMax;

@@ -122,6 +122,7 @@ constexpr int kGram10U = BBL_GRAM10_U;
 constexpr int kG16CG = BBL_G16_CG, kG16U = BBL_G16_U, kG16Waves = BBL_G16_WAVES;
 constexpr int kG16MinWaves = BBL_G16_MIN_WAVES, kG16MinRows = BBL_G16_MIN_ROWS;
 constexpr int kU16U = BBL_U16_U, kU16Waves = BBL_U16_WAVES;
+constexpr int kU16SplitU = 2;
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 // partial[p][m][c] for p = blockIdx.x (row chunk), m in this WG's tile group.
@@ -415,28 +416,33 @@ __global__ __launch_bounds__(64) void k_gram_mfma16(int64_t n, const XT *__restr
 // t + (l & 15) of the tile, basis columns 4k .. 4k + 3 (component q is column
 // 4k + q); B operand (q, h): C[16 blk + 4k + q][4j + h], j = l & 3, which each
 // lane loads per block (four 32-byte runs); D(h)[i][j] at lane 16i + 4g + j is
-// Yout[t + 4g + i][4j + h].  A wave strides over tiles of 16 U rows.
+// Yout[t + 4g + i][4j + h].  A wave strides over tiles of 16 U rows; with
+// WS > 1 the WS waves of a workgroup share one tile, wave w taking blocks w,
+// w + WS, ..., and the first adds their sums in fixed order and finishes it.
 // GRAM: the wave also sums the Gram matrix of the values it stored: as an A
 // (or B) operand, lane 16k + 4g + j holds row t + 4g + k, columns 4j + h, so
 // the output registers feed sixteen more products per tile directly;
 // gpart[wave][16][16], the four groups' sums added by lane shuffles.
-template <typename XT, typename YIT, typename YOT, int U, bool GRAM>
-__global__ __launch_bounds__(64) void k_update_mfma16(int64_t n, const XT *__restrict__ X, int nblk,
-                                                      int64_t xstride, const double *__restrict__ C,
-                                                      double alpha, const YIT *Yin, double beta,
-                                                      YOT *Yout, const int *__restrict__ when,
-                                                      double *__restrict__ gpart) {
+template <typename XT, typename YIT, typename YOT, int U, bool GRAM, int WS>
+__global__ __launch_bounds__(64 * WS, WS > 1 ? 4 : 1) void k_update_mfma16(
+    int64_t n, const XT *__restrict__ X, int nblk, int64_t xstride, const double *__restrict__ C,
+    double alpha, const YIT *Yin, double beta, YOT *Yout, const int *__restrict__ when,
+    double *__restrict__ gpart) {
   if (when && *when == 0) return;
-  const int l = threadIdx.x;
+  __shared__ double part[WS > 1 ? WS : 1][WS > 1 ? U * 4 * 64 : 1];
+  const int l = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int kq = l >> 4, e = l & 3, ra = l & 15;     // A operand: quarter kq of row ra
   const int rd = 4 * ((l >> 2) & 3) + (l >> 4);      // D: row of the tile this lane holds
   double gacc[GRAM ? 4 : 1][GRAM ? 4 : 1];
-  if constexpr (GRAM) {
+  auto clear = [&] {
+    if constexpr (GRAM) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+      for (int q = 0; q < 4; ++q)
 #pragma unroll
-      for (int h = 0; h < 4; ++h) gacc[q][h] = 0.0;
-  }
+        for (int h = 0; h < 4; ++h) gacc[q][h] = 0.0;
+    }
+  };
+  if constexpr (WS == 1) clear();
   const int64_t tiles = (n + 16 * U - 1) / (16 * U);
   for (int64_t tt = blockIdx.x; tt < tiles; tt += gridDim.x) {
     const int64_t t = tt * (16 * U);
@@ -445,7 +451,8 @@ __global__ __launch_bounds__(64) void k_update_mfma16(int64_t n, const XT *__res
     for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int h = 0; h < 4; ++h) acc[u][h] = 0.0;
-    for (int blk = 0; blk < nblk; ++blk) {
+#pragma unroll 1
+    for (int blk = wave; blk < nblk; blk += WS) {
       double cb[4][4];
       const double *cp = C + ((int64_t)blk * 16 + 4 * kq) * 16 + 4 * e;
 #pragma unroll
@@ -467,6 +474,21 @@ __global__ __launch_bounds__(64) void k_update_mfma16(int64_t n, const XT *__res
           for (int h = 0; h < 4; ++h)
             acc[u][h] = __builtin_amdgcn_mfma_f64_4x4x4f64((double)x[u][q], cb[q][h], acc[u][h],
                                                            0, 0, 0);
+    }
+    if constexpr (WS > 1) {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int h = 0; h < 4; ++h) part[wave][(u * 4 + h) * 64 + l] = acc[u][h];
+      __syncthreads();
+      if (wave) return;  // one tile a workgroup: no barrier follows
+#pragma unroll 2
+      for (int w = 1; w < WS; ++w)
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int h = 0; h < 4; ++h) acc[u][h] += part[w][(u * 4 + h) * 64 + l];
+      clear();
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -494,6 +516,7 @@ __global__ __launch_bounds__(64) void k_update_mfma16(int64_t n, const XT *__res
             gacc[q][h] = __builtin_amdgcn_mfma_f64_4x4x4f64(o[q], o[h], gacc[q][h], 0, 0, 0);
       }
     }
+    if constexpr (WS > 1) break;
   }
   if constexpr (GRAM) {
 #pragma unroll
@@ -1173,12 +1196,11 @@ __global__ __launch_bounds__(512) void k_update_w8(int64_t n, const XT *X, int n
                                                    double alpha, const YIT *Yin, double beta,
                                                    YOT *Yout, const int *__restrict__ when,
                                                    double *__restrict__ gpart) {
-  static_assert(NY <= 8, "one component per wave");
-  static_assert(BX * NY <= 64, "one C entry per lane");
+  constexpr int CL = (BX * NY + 63) / 64;  // C entries a lane
   constexpr int NP = NY * (NY + 1) / 2;
   constexpr int S = 512 / NP;  // slices per Gram entry
   if (when && *when == 0) return;
-  __shared__ double part[8][64][NY];
+  __shared__ double part[8][NY][64];
   __shared__ double gt[GRAM ? 64 : 1][NY + 1];
   __shared__ double red[GRAM ? 512 : 1];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -1194,27 +1216,36 @@ __global__ __launch_bounds__(512) void k_update_w8(int64_t n, const XT *X, int n
     else
 #pragma unroll
       for (int c = 0; c < BX; ++c) xv.v[c] = XT(0);
-    const double cl = lane < BX * NY ? C[(int64_t)blk * BX * NY + lane] : 0.0;
+    double cl[CL];
+#pragma unroll
+    for (int c = 0; c < CL; ++c)
+      cl[c] = 64 * c + lane < BX * NY ? C[(int64_t)blk * BX * NY + 64 * c + lane] : 0.0;
 #pragma unroll
     for (int a = 0; a < BX; ++a)
 #pragma unroll
-      for (int j = 0; j < NY; ++j) acc[j] = fma((double)xv.v[a], readlane_f64(cl, a * NY + j), acc[j]);
+      for (int j = 0; j < NY; ++j) {
+        const int e = a * NY + j;
+        acc[j] = fma((double)xv.v[a], readlane_f64(cl[e / 64], e % 64), acc[j]);
+      }
   }
 #pragma unroll
-  for (int j = 0; j < NY; ++j) part[w][lane][j] = acc[j];
+  for (int j = 0; j < NY; ++j) part[w][j][lane] = acc[j];
   __syncthreads();
-  double o = 0.0;
-  if (w < NY && r < n) {
-    double v = 0.0;
 #pragma unroll
-    for (int q = 0; q < 8; ++q) v += part[q][lane][w];
-    o = beta != 0.0 ? fma(beta, (double)Yin[r * NY + w], alpha * v) : alpha * v;
-    const YOT ov = (YOT)o;
-    Yout[r * NY + w] = ov;
-    o = (double)ov;
+  for (int j = w; j < NY; j += 8) {
+    double o = 0.0;
+    if (r < n) {
+      double v = 0.0;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v += part[q][j][lane];
+      o = beta != 0.0 ? fma(beta, (double)Yin[r * NY + j], alpha * v) : alpha * v;
+      const YOT ov = (YOT)o;
+      Yout[r * NY + j] = ov;
+      o = (double)ov;
+    }
+    if constexpr (GRAM) gt[lane][j] = o;
   }
   if constexpr (GRAM) {
-    if (w < NY) gt[lane][w] = o;
     __syncthreads();
     const int t = threadIdx.x;
     double gsum = 0.0;
@@ -1482,10 +1513,16 @@ inline int64_t update_tiles(int64_t n) { return ceil_div(n, 256 * kUpdRPL); }
 inline int64_t update_gram_parts(int64_t n) {
   return std::min<int64_t>(update_tiles(n), kUpdMaxGramParts);
 }
-// the wave-split kernel k_update_w8 (short grids, many blocks); its Gram
-// partials are one per 64 rows
+// the wave-split kernel k_update_w8 (short grids, several blocks); its Gram
+// partials are one per 64 rows.  Against a lane walking all blocks of its row
+// (k_update_v): 8 FP32 blocks of 8, n = 20,000 4.9 against 11.1 us, n = 130,000
+// 13.8 against 20.6; 45 FP64 blocks of 10, n = 20,000 20 against 108, n =
+// 250,000 177 against 175.  Fewer blocks leave waves idle: 4 of 8, n = 60,000
+// 5.8 against 7.7, n = 130,000 10.0 against 9.1; 8 of 4, n = 130,000 5.6
+// against 6.4, n = 250,000 11.8 against 11.5.
 inline bool update_split(int64_t n, int nblk, int ny) {
-  return update_tiles(n) < 512 && nblk >= 16 && ny <= 8;
+  return ny <= 10 && update_tiles(n) < 512 &&
+         nblk >= (n <= 65536 ? 4 : n <= 131072 ? 8 : 16);
 }
 inline int64_t update_parts(int64_t n, int nblk, int ny) {
   return update_split(n, nblk, ny) ? ceil_div(n, 64) : update_gram_parts(n);
@@ -1500,7 +1537,7 @@ void update_valu(int64_t n, const XT *X, int nblk, int64_t xstride, const double
   // (no fused Gram then); a short grid with a few blocks: prefetch four at a
   // time
   if (update_split(n, nblk, NY)) {
-    if constexpr (NY <= 8) {
+    if constexpr (NY <= 10) {
       const dim3 grid8((unsigned)ceil_div(n, 64)), wg8(512);
       if (gpart)
         hipLaunchKernelGGL((k_update_w8<XT, YIT, YOT, B, NY, true>), grid8, wg8, 0, s, n,
@@ -1531,21 +1568,42 @@ void update_valu(int64_t n, const XT *X, int nblk, int64_t xstride, const double
   check_launch("k_update_v");
 }
 
+// Blocks split over the eight waves of a workgroup (k_update_mfma16, WS = 8)
+// where one wave a tile leaves the chip waiting for its serial loads of basis
+// and C: FP32, n = 20,000, 4 / 8 / 45 blocks 5.1 / 6.1 / 18 us against 7.2 / 11
+// / 76; 60,000 rows 9.1 / 13 / 40 against 8.8 / 19 / 82; 130,000 rows, 8 / 16 /
+// 45 blocks 24 / 35 / 108 against 24 / 41 / 136; 250,000 rows, 45 blocks 200
+// against 186.  FP64 tiles carry twice the bytes: 27 against 46 us at 20,000
+// rows and 45 blocks, 78 against 68 at 60,000.
+inline bool update16_split(int64_t n, int nblk, bool xf32) {
+  if (n <= 32768) return nblk >= 4;
+  return xf32 && n <= 131072 && nblk >= (n <= 65536 ? 8 : 16);
+}
+inline int64_t update16_parts(int64_t n, int nblk, bool xf32) {
+  if (update16_split(n, nblk, xf32)) return ceil_div(n, 16 * kU16SplitU);
+  return std::min<int64_t>(ceil_div(n, 16 * kU16U), kU16Waves);
+}
 // 16-wide blocks on FP64 matrix cores; the fused Gram needs (P + P/8 + 64)
 // x 256 doubles of gpart (partials and the reduction's second stage).
 template <typename XT, typename YIT, typename YOT>
 int update_mfma16(int64_t n, const XT *X, int nblk, int64_t xstride, const double *C,
                   double alpha, const YIT *Yin, double beta, YOT *Yout, const int *when,
                   double *gpart, size_t gcap_doubles, hipStream_t s) {
-  constexpr int U = kU16U;
-  const int64_t P = std::max<int64_t>(1, std::min<int64_t>(ceil_div(n, 16 * U), kU16Waves));
+  constexpr bool xf32 = std::is_same<XT, float>::value;
+  const int64_t P = update16_parts(n, nblk, xf32);
   if (gpart && (size_t)(P + P / 8 + 64) * 256 > gcap_doubles) gpart = nullptr;
-  if (gpart)
-    hipLaunchKernelGGL((k_update_mfma16<XT, YIT, YOT, U, true>), dim3((unsigned)P), dim3(64), 0, s,
-                       n, X, nblk, xstride, C, alpha, Yin, beta, Yout, when, gpart);
-  else
-    hipLaunchKernelGGL((k_update_mfma16<XT, YIT, YOT, U, false>), dim3((unsigned)P), dim3(64), 0,
-                       s, n, X, nblk, xstride, C, alpha, Yin, beta, Yout, when, nullptr);
+  const bool split = update16_split(n, nblk, xf32);
+#define BBL_U16L(U, G, WS)                                                                       \
+  hipLaunchKernelGGL((k_update_mfma16<XT, YIT, YOT, U, G, WS>), dim3((unsigned)P), dim3(64 * WS), \
+                     0, s, n, X, nblk, xstride, C, alpha, Yin, beta, Yout, when, gpart)
+  if (gpart) {
+    if (split) BBL_U16L(kU16SplitU, true, 8);
+    else BBL_U16L(kU16U, true, 1);
+  } else {
+    if (split) BBL_U16L(kU16SplitU, false, 8);
+    else BBL_U16L(kU16U, false, 1);
+  }
+#undef BBL_U16L
   check_launch("k_update_mfma16");
   return gpart ? (int)P : 0;
 }
@@ -1650,9 +1708,8 @@ int launch_reduce_parts(const double *partial, int P, int MN, double *tmp, hipSt
   return S;
 }
 
-int64_t update_gram_parts(int64_t n, int nblk, int b) {
-  return b == 16 ? std::max<int64_t>(1, std::min<int64_t>(ceil_div(n, 16 * kU16U), kU16Waves))
-                 : update_parts(n, nblk, b);
+int64_t update_gram_parts(int64_t n, int nblk, int b, int xdtype) {
+  return b == 16 ? update16_parts(n, nblk, xdtype == BBL_F32) : update_parts(n, nblk, b);
 }
 
 void launch_reduce(const double *partial, int P, int M, int ny, double *out, hipStream_t s) {

@@ -499,6 +499,29 @@ def test_gram_of_narrow_blocks_at_its_edges(torch, bbl, bx, xf32, yf32, nblk):
         assert np.all(np.abs(C.reshape(bound.shape) - Xwide.T @ Y) <= bound), n
 
 
+@pytest.mark.parametrize("xf32", [True, False])
+@pytest.mark.parametrize("bx,ny", [(4, 4), (8, 8), (8, 10), (10, 10), (16, 16)])
+def test_update_split_over_waves_at_its_edges(torch, bbl, bx, ny, xf32):
+    """Block counts below, at and above one for each of the eight waves, row
+    counts around a tile (32 and 64 rows) and around the limits of the split
+    (32,768, 65,536 and 131,072 rows), out of place and in place."""
+    rng = np.random.default_rng(10 * bx + ny)
+    for n, nblk in ((1, 4), (31, 3), (33, 4), (64, 5), (65, 8), (4099, 9), (20_001, 17),
+                    (32_768, 4), (32_769, 4), (65_536, 7), (65_537, 7), (65_537, 8), (131_073, 8)):
+        note("update edges bx=%d ny=%d n=%d nblk=%d x32=%s" % (bx, ny, n, nblk, xf32))
+        Xb = rng.standard_normal((nblk, n, bx)).astype(np.float32 if xf32 else np.float64)
+        Y, Cm = rng.standard_normal((n, ny)), rng.standard_normal((nblk * bx, ny))
+        Xwide = np.concatenate(list(Xb.astype(np.float64)), axis=1)
+        ref = Y - Xwide @ Cm
+        tol = 64 * nblk * bx * U64 * (np.abs(Y) + np.abs(Xwide) @ np.abs(Cm))
+        Xd, Yd, Out = dev(torch, Xb), dev(torch, Y), torch.empty((n, ny), dtype=torch.float64,
+                                                                 device="cuda")
+        bbl.block_update(Xd, nblk, bx, dev(torch, Cm), -1.0, Yd, 1.0, Out)
+        assert np.all(np.abs(Out.cpu().numpy() - ref) <= tol), (n, nblk)
+        bbl.block_update(Xd, nblk, bx, dev(torch, Cm), -1.0, Yd, 1.0, Yd)
+        assert torch.equal(Yd, Out), (n, nblk)
+
+
 @pytest.mark.parametrize("n", [1, 7, 17, 33])
 def test_sixteen_wide_products_on_tiny_row_counts(torch, bbl, n):
     """The 16-wide matrix-core gram and update on fewer rows than one 16-row

@@ -1245,6 +1245,30 @@ __device__ __forceinline__ T halving_partner(T x, int off) {
   if (off == 2) return dpp_f<0x4E>(x);
   return dpp_f<0xB1>(x);
 }
+// The halving exchange itself, from round OFF down: v[0 .. K) in, the lane's
+// sums in the front of v out (once one is left the remaining rounds add it
+// up, so lanes that differ in their low bits end with the same).  The selects
+// are on values: written on array elements they choose an address, which
+// became a comparison per element, 200 instructions at the end of a row of
+// the 16-column product (n = 2e6, 400 nonzeros a row: 2341 us, now 2270).  At
+// fewer columns than lanes it replaces row16_sum per column (b = 4, 1e6 rows
+// of 160: 261 us, now 248; FP64, b = 8, 4e5 rows of 62: 216 us, now 208).
+template <bool PAIR, int OFF, int K, typename T, int N>
+__device__ __forceinline__ void halving_sums(T (&v)[N], int sub) {
+  if constexpr (OFF >= (PAIR ? 2 : 1)) {
+    if constexpr (K == 1) {
+      v[0] += halving_partner<PAIR>(v[0], OFF);
+    } else {
+      const bool up = sub & OFF;
+#pragma unroll
+      for (int i = 0; i < K / 2; ++i) {
+        const T lo = v[i], hi = v[i + K / 2];
+        v[i] = (up ? hi : lo) + halving_partner<PAIR>(up ? lo : hi, OFF);
+      }
+    }
+    halving_sums<PAIR, OFF / 2, (K > 1 ? K / 2 : 1)>(v, sub);
+  }
+}
 template <typename T>
 __device__ __forceinline__ T row16_sum(T v) {
   v += dpp_f<0xB1>(v);   // quad_perm [1, 0, 3, 2]
@@ -1545,12 +1569,17 @@ __device__ __forceinline__ void pipe_run(int64_t g, int64_t n, int64_t G, int sl
   // A finished row's sums, stored at the start of the following step: a store
   // issued after the step's loads would have to complete before the next
   // step's first wait.
-  constexpr int NOUT = kRot ? 1 : (BL >= LPE ? NO : BL);
+  // fewer columns than lanes, a power of two of them: the halving exchange
+  // leaves one sum a lane, the LPE / BL lanes of a component the same one
+  constexpr bool kOne = !kRot && BL < LPE && (BL & (BL - 1)) == 0;
+  constexpr int NOUT = kRot || kOne ? 1 : (BL >= LPE ? NO : BL);
   T out[NOUT];
   T *yp = nullptr;
   auto store_out = [&]() __attribute__((always_inline)) {
     if constexpr (kRot) {
       if ((sub & 1) == 0) yp[sub >> 1] = out[0];
+    } else if constexpr (kOne) {
+      if (sub % (LPE / BL) == 0) yp[sub / (LPE / BL)] = out[0];
     } else if constexpr (BL >= LPE) {
       pipe_vstore<NO>(yp + cb, out);
     } else {
@@ -1644,23 +1673,22 @@ __device__ __forceinline__ void pipe_run(int64_t g, int64_t n, int64_t G, int sl
         T v[BL];
 #pragma unroll
         for (int a = 0; a < BL; ++a) v[a] = acc[a];
-#pragma unroll
-        for (int off = LPR / 2, K = BL; off >= (PAIR ? 2 : 1); off >>= 1, K >>= 1) {
-          const bool up = sub & off;
-#pragma unroll
-          for (int i = 0; i < K / 2; ++i) {
-            const T send = up ? v[i] : v[i + K / 2];
-            const T keep = up ? v[i + K / 2] : v[i];
-            v[i] = keep + halving_partner<PAIR>(send, off);
-          }
-        }
+        halving_sums<PAIR, LPR / 2, BL>(v, sub);
 #pragma unroll
         for (int i = 0; i < NO; ++i) out[i] = v[i] + (P2 ? cur.yp[i] : T(0));
       } else {
         static_assert(!P2 && !PAIR, "pass 2 and lane pairs need BL >= LPE");
         static_assert(LPR == 16, "one DPP row per matrix row");
+        if constexpr (kOne) {
+          T v[BL];
 #pragma unroll
-        for (int a = 0; a < B; ++a) out[a] = row16_sum(acc[a]);
+          for (int a = 0; a < BL; ++a) v[a] = acc[a];
+          halving_sums<false, LPR / 2, BL>(v, sub);
+          out[0] = v[0];
+        } else {
+#pragma unroll
+          for (int a = 0; a < B; ++a) out[a] = row16_sum(acc[a]);
+        }
       }
 #pragma unroll
       for (int a = 0; a < BL; ++a) acc[a] = T(0);

@@ -174,27 +174,41 @@ def _check(code):
     return code
 
 
+_torch_mod = None
+_dtype_codes = {}
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_mod
+    if _torch_mod is None:
+        import torch
+        _dtype_codes.update({torch.float32: BBL_F32, torch.float64: BBL_F64})
+        _torch_mod = torch
+    return _torch_mod
 
 
+# A small product's kernel takes 6 us, less than marshalling its call did (8.6 us
+# a call): a Stream object per call was a third of that, c_void_p objects and
+# dtype comparisons most of the rest.  The arguments go as plain integers (the
+# signatures convert them), the stream as its raw handle.
 def _stream():
     torch = _torch()
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch._C._cuda_getDevice())
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
 
 
 def _dtype_code(t):
-    torch = _torch()
-    if t.dtype == torch.float32:
-        return BBL_F32
-    if t.dtype == torch.float64:
-        return BBL_F64
-    raise TypeError("only float32 / float64 tensors are supported, got %s" % t.dtype)
+    _torch()
+    code = _dtype_codes.get(t.dtype)
+    if code is None:
+        raise TypeError("only float32 / float64 tensors are supported, got %s" % t.dtype)
+    return code
 
 
 @dataclass

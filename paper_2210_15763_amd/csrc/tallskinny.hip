@@ -451,7 +451,6 @@ __global__ __launch_bounds__(64 * WS, WS > 1 ? 4 : 1) void k_update_mfma16(
     for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int h = 0; h < 4; ++h) acc[u][h] = 0.0;
-#pragma unroll 1
     for (int blk = wave; blk < nblk; blk += WS) {
       double cb[4][4];
       const double *cp = C + ((int64_t)blk * 16 + 4 * kq) * 16 + 4 * e;

@@ -155,7 +155,7 @@ def _per_dispatch(rows, counter, match):
     return float(np.mean(list(per.values()))), len(per)
 
 
-SPMM_PASSES = ("k_spmm_pipe12<8, false, float>", "k_spmm_rest<8, false, float>")
+SPMM_PASSES = ("k_spmm_pipe12<8, false, float, ", "k_spmm_rest<8, false, float>")
 REORTH_BLOCKS = 50   # basis blocks of the counter runs' gram and update
 
 
@@ -198,7 +198,7 @@ def write_traffic(fetch_dir, write_dir):
     # same n: the gram reads the basis and W' (FP64), the update reads both
     # and writes W'
     n, b, M = H.n, w.nvec, REORTH_BLOCKS * w.nvec
-    kern = {"gram": ("k_gram_mfma8", 4 * n * M + 8 * n * b),
+    kern = {"gram": ("k_gram_quads<float, ", 4 * n * M + 8 * n * b),
             "update": ("k_update_v<float, double, double", 4 * n * M + 16 * n * b)}
     rr = {"workload": "FP32 basis of %d blocks of %d vectors, n=%d; FP64 W'" % (REORTH_BLOCKS, b, n),
           "tallskinny_source_hash": source_hash("tallskinny.hip"),

@@ -167,6 +167,30 @@ def test_planned_spmm_matches_oracle(torch, bbl, nvec, block_rows, prec, q, p):
     assert np.all(np.abs(W - oracle.spmm(Href, Vr)) <= bound)
 
 
+@pytest.mark.parametrize("nvec,block_rows,prec", [
+    (8, 1000, "f32"), (8, 2000, "f32"), (8, 1000, "f64"), (4, 1000, "f32"), (4, 1000, "f64"),
+    (10, 1000, "f32"), (16, 1000, "f32"), (16, 2000, "f32"), (16, 400, "f32")])
+@pytest.mark.parametrize("q", [1, 4, 37, 43])
+def test_planned_spmm_lane_splits(torch, bbl, nvec, block_rows, prec, q):
+    """Rows of 1 to 128 entries, on average 3, 9, 74 and 86 (8 or 16 lanes a row
+    in pass 1 below and above 80; sets with no, one or two steps of a row), the
+    last group of 400 or 2000 rows ragged: the dot-product bound entry by
+    entry."""
+    note("planned spmm lanes block_rows=%d nvec=%d %s q=%d" % (block_rows, nvec, prec, q))
+    H = synthgen.generate(21000, 1000, q, 0.6, 17)
+    Hd = bbl.DeviceCSR.from_host(H, "float32" if prec == "f32" else "float64",
+                                 block_rows=block_rows)
+    plan = bbl.spmm_plan(Hd, nvec)
+    V = synthgen.gaussian_block(H.n, nvec, 7)
+    u = U32 if prec == "f32" else U64
+    if prec == "f32":
+        H, V = H.as_float32_values(), V.astype(np.float32).astype(np.float64)
+    W = bbl.spmm_planned(plan, dev(torch, V.astype(np.float32) if prec == "f32" else V))
+    z = np.diff(H.row_ptr)[:, None]
+    bound = gamma(z + 2, u) * oracle.spmm_abs(H, V) + 1e-300
+    assert np.all(np.abs(W.double().cpu().numpy() - oracle.spmm(H, V)) <= bound)
+
+
 @pytest.mark.parametrize("n,R,q,p,nvec,block_rows", [
     (40000, 2000, 105, 0.7, 8, 2000), (40000, 2000, 105, 0.7, 16, 2000),
     (40000, 2000, 105, 0.7, 10, 2000), (40000, 1000, 60, 0.5, 4, 5000),

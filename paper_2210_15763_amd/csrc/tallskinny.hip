@@ -1172,10 +1172,10 @@ __global__ __launch_bounds__(256) void k_update_v(int64_t n, const XT *X, int nb
 // alpha X C with the basis blocks split over the eight waves of a workgroup
 // (wave w takes blocks w, w + 8, ...) and one row per lane, so the grid holds
 // eight times as many waves as one row per lane over all blocks would; the
-// eight partial sums of each row are added in LDS in fixed order, thread t
-// finishing component t / 64 of row t % 64.  Lane l loads entry l of a
-// block's BX x NY slice of C (one vector load per block) and the products
-// take the entries with v_readlane: scalar loads of C, whose slices of all
+// eight partial sums of each row are added in LDS in fixed order, wave w
+// finishing components w and w + 8.  Lane l loads entries l, l + 64 of a
+// block's BX x NY slice of C (one or two vector loads per block) and the
+// products take the entries with v_readlane: scalar loads of C, whose slices of all
 // blocks do not fit the scalar cache, ran at half this speed (n = 20,000,
 // 91 blocks: 48 against 26 us).
 //
@@ -1532,9 +1532,8 @@ void update_valu(int64_t n, const XT *X, int nblk, int64_t xstride, const double
                  const YIT *Yin, double beta, YOT *Yout, const int *when, double *gpart,
                  hipStream_t s) {
   const int64_t grid = gpart ? update_gram_parts(n) : update_tiles(n);
-  // a short grid (few rows) with many blocks: split the blocks over waves
-  // (no fused Gram then); a short grid with a few blocks: prefetch four at a
-  // time
+  // a short grid (few rows) with several blocks: split the blocks over waves;
+  // otherwise prefetch four at a time
   if (update_split(n, nblk, NY)) {
     if constexpr (NY <= 10) {
       const dim3 grid8((unsigned)ceil_div(n, 64)), wg8(512);

@@ -266,6 +266,13 @@ struct BandStage {
   __device__ __forceinline__ BandStage(const double *Tb_, int N, int pad, double *buf_, int lane_)
       : Tb(Tb_), buf(buf_), next((int64_t)(W - pad) * W), last((int64_t)N * W - 1), lane(lane_) {
     load();
+    // slots d > i of row i hold no entry of the matrix, whatever is in them; of
+    // the entering rows only those of the first chunk (of at least W) have any
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int i = (W - pad) * W + lane + 64 * u;
+      if (i % W > i / W) pre[u] = 0.0;
+    }
   }
   __device__ __forceinline__ void load() {
 #pragma unroll

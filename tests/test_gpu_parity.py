@@ -655,6 +655,31 @@ def test_band_eig_split_edges(torch, bbl, kd, shape):
         assert np.max(np.abs(Sg.T @ Sg - np.eye(k))) <= 1e-12
 
 
+@pytest.mark.parametrize("entry", ["band_eig", "band_eig_noalloc"])
+@pytest.mark.parametrize("kd", [1, 2, 3, 4, 8, 10, 16])
+def test_band_eig_ignores_slots_outside_the_matrix(torch, bbl, kd, entry):
+    """band[i][d] with d > i is no entry of the matrix, so what is there (ones,
+    NaN) changes no bit of the result; short matrices, every padding of the
+    two-sided factorisation, and factors too large for LDS."""
+    w = kd + 1
+    sizes = [max(1, kd - 1), kd, w, 2 * w, 3 * w - 1]
+    sizes += list(range(4 * w + kd, 5 * w + kd)) + [min(20400 // (kd + 2), 7001)]
+    for N in sizes:
+        k = min(N, 5)
+        note("band eig slots outside N=%d kd=%d %s" % (N, kd, entry))
+        rng = np.random.default_rng(7 * N + kd)
+        band = rng.standard_normal((N, w))
+        band[:, 0] += np.linspace(-20, 20, N)
+        outside = np.arange(w)[None, :] > np.arange(N)[:, None]
+        got = []
+        for fill in (0.0, 1.0, np.nan):
+            band[outside] = fill
+            theta, S, top = getattr(bbl, entry)(dev(torch, band), N, kd, k)
+            got.append(np.concatenate([theta, [top], S.cpu().numpy().ravel()]))
+        assert np.all(np.isfinite(got[0]))
+        assert np.array_equal(got[0], got[1]) and np.array_equal(got[0], got[2])
+
+
 @pytest.mark.parametrize("kd", [4, 6])
 def test_band_eig_double_eigenvalues(torch, bbl, kd):
     """T = diag(B, B): every eigenvalue twice.  Inverse iteration at equal

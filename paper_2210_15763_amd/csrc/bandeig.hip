@@ -1200,10 +1200,14 @@ __device__ void write_results(int t, int N, int k, const double *__restrict__ Bj
 // Rayleigh-Ritz on span(X): X <- orthonormal basis (modified Gram-Schmidt,
 // twice), K = X^T T X, K = Y diag(theta) Y^T, S = X Y.  K, Y: kMaxBlock^2
 // doubles of LDS each; lam: kMaxBlock; cs: 4; red: one per thread.
-__device__ void rr_gram_schmidt(const double *__restrict__ Tb, int N, int kd, int k, double *X,
-                                double *TX, const double *__restrict__ Bj, int b,
-                                const double *__restrict__ brk, double *S, double *res, double *K,
-                                double *Y, double *lam, double *cs, double *red) {
+// Inlined into k_rr, so that its LDS is addressed as LDS (as a call, through flat
+// addresses, k_rr took 6.69 ms at N = 1136, kd = 16, k = 32; inlined 6.11).
+__device__ __forceinline__ void rr_gram_schmidt(const double *__restrict__ Tb, int N, int kd,
+                                                int k, double *X, double *TX,
+                                                const double *__restrict__ Bj, int b,
+                                                const double *__restrict__ brk, double *S,
+                                                double *res, double *K, double *Y, double *lam,
+                                                double *cs, double *red) {
   const int t = threadIdx.x;
   for (int c = 0; c < k; ++c) {
     for (int attempt = 0; attempt < 2; ++attempt) {
@@ -1276,6 +1280,16 @@ __global__ __launch_bounds__(256) void k_rr(const double *__restrict__ Tb, int N
                                             double *res) {
   __shared__ double K[kMaxBlock * kMaxBlock], Y[kMaxBlock * kMaxBlock];
   __shared__ double lam[kMaxBlock], cs[4], red[256];
+  rr_gram_schmidt(Tb, N, kd, k, X, TX, Bj, b, brk, S, res, K, Y, lam, cs, red);
+}
+
+// The same for k_rr_fast, which rarely needs it and would spill more registers
+// with it inlined.
+__device__ __noinline__ void rr_gram_schmidt_call(const double *Tb, int N, int kd, int k,
+                                                  double *X, double *TX, const double *Bj, int b,
+                                                  const double *brk, double *S, double *res,
+                                                  double *K, double *Y, double *lam, double *cs,
+                                                  double *red) {
   rr_gram_schmidt(Tb, N, kd, k, X, TX, Bj, b, brk, S, res, K, Y, lam, cs, red);
 }
 
@@ -1460,8 +1474,8 @@ __global__ __launch_bounds__(64 * kRrWaves) void k_rr_fast(
     if (sbad) {
       double *K = stage, *Y = stage + kMaxBlock * kMaxBlock;
       __syncthreads();
-      rr_gram_schmidt(Tb, N, kd, k, X, Qg, Bj, b, brk, S, res, K, Y, lam, cs,
-                      Y + kMaxBlock * kMaxBlock);
+      rr_gram_schmidt_call(Tb, N, kd, k, X, Qg, Bj, b, brk, S, res, K, Y, lam, cs,
+                           Y + kMaxBlock * kMaxBlock);
       return;
     }
     times(M1, Q);

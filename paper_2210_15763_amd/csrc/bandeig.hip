@@ -1566,11 +1566,12 @@ bool reg_bandwidth(int kd) {
 }
 int shifts_per_target(int nsh, int NT) { return std::max(64, (nsh / NT) / 64 * 64); }
 
-// Lets a kernel use up to `bytes` of dynamic LDS; kept in a function's static,
-// so once per process and kernel.
-bool allow_lds(const void *kernel, size_t bytes) {
-  BBL_HIP(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
-  return true;
+// Lets a kernel use up to `bytes` of dynamic LDS on the current device.  Each
+// device has its own limit, so it is set before each launch.
+template <typename K>
+void allow_lds(K *kernel, size_t bytes) {
+  BBL_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
 }
 
 template <int KD>
@@ -1579,8 +1580,7 @@ void invit_reg_launch(const double *band, const double *rev, int N, const Bisect
   const int k = B.k;
   const size_t two = ((size_t)N * (KD + 2) + invit_two_extra<KD>()) * sizeof(double);
   if (N >= KD && two <= kInvLds) {
-    static const bool ok = allow_lds(reinterpret_cast<const void *>(&k_invit_two<KD>), kInvLds);
-    (void)ok;
+    allow_lds(&k_invit_two<KD>, kInvLds);
     hipLaunchKernelGGL(k_invit_two<KD>, dim3(k + 1), dim3(128), two, s, band, rev, N, B, rounds,
                        kInvPivmin, brk, X, kInvIters);
     check_launch("k_invit_two");
@@ -1590,9 +1590,7 @@ void invit_reg_launch(const double *band, const double *rev, int N, const Bisect
   check_launch("k_final_brackets");
   const size_t xbytes = (size_t)N * k * sizeof(double);
   if (xbytes <= kInvLds) {
-    static const bool ok =
-        allow_lds(reinterpret_cast<const void *>(&k_invit_reg<KD, true>), kInvLds);
-    (void)ok;
+    allow_lds(&k_invit_reg<KD, true>, kInvLds);
     hipLaunchKernelGGL((k_invit_reg<KD, true>), dim3(1), dim3(64), xbytes, s, band, N, brk, k,
                        kInvPivmin, Lscr, Dscr, X, kInvIters);
   } else {
@@ -1685,8 +1683,7 @@ void band_eigensolve(const double *band, int N, int kd, int k, void *ws, const B
     }
     const size_t smem = (size_t)((kd + 1) * (kd + 1) + kChunk * (kd + 1) + N) * sizeof(double);
     BBL_REQUIRE(smem <= 150 * 1024, "band eigensolve: band matrix too large for LDS staging");
-    static const bool ok = allow_lds(reinterpret_cast<const void *>(&k_invit), 150 * 1024);
-    (void)ok;
+    allow_lds(&k_invit, 150 * 1024);
     hipLaunchKernelGGL(k_invit, dim3(k), dim3(64), smem, s, band, N, kd, brk, k, kInvPivmin, Lscr,
                        Dscr, X, kInvIters);
     check_launch("k_invit");
@@ -1695,8 +1692,7 @@ void band_eigensolve(const double *band, int N, int kd, int k, void *ws, const B
   if (k <= kRrMax) {
     const size_t qbytes = (size_t)N * k * sizeof(double);
     if (qbytes <= kRrLds) {
-      static const bool ok = allow_lds(reinterpret_cast<const void *>(&k_rr_fast<true>), kRrLds);
-      (void)ok;
+      allow_lds(&k_rr_fast<true>, kRrLds);
       hipLaunchKernelGGL(k_rr_fast<true>, dim3(1), dim3(64 * kRrWaves), qbytes, s, band, N, kd, k,
                          X, TX, Bj, b, brk, S, res);
     } else {

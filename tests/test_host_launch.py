@@ -1,0 +1,65 @@
+"""The launches the library's host code makes, on the CPU: its host objects
+linked against a stand-in for the HIP runtime (tests/host_launch/probe.cpp)
+that records kernels, grids and dynamic LDS."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2210_15763_amd", "csrc")
+HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+CLANG = "/opt/rocm/llvm/bin/clang++"
+
+pytestmark = pytest.mark.skipif(not (os.path.exists(HIPCC) and os.path.exists(CLANG)),
+                                reason="hipcc / ROCm clang not found")
+
+
+@pytest.fixture(scope="module")
+def launches(tmp_path_factory):
+    """launches(calls): for each call (a line of text) its output lines."""
+    tmp = str(tmp_path_factory.mktemp("host_launch"))
+    srcs = [os.path.join(CSRC, f) for f in ("bandeig.hip", "spmm.hip", "tallskinny.hip")]
+    srcs.append(os.path.join(ROOT, "tests", "host_launch", "probe.cpp"))
+    jobs, objs = [], []
+    for src in srcs:
+        objs.append(os.path.join(tmp, os.path.basename(src) + ".o"))
+        cmd = [HIPCC, "--offload-arch=gfx950", "--offload-host-only", "-x", "hip", "-O0", "-g0",
+               "-std=c++17", "-Wno-unused-command-line-argument", "-I" + CSRC, "-c", src, "-o",
+               objs[-1]]
+        jobs.append(subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT,
+                                     text=True))
+    for p in jobs:
+        out = p.communicate()[0]
+        assert p.returncode == 0, out[-4000:]
+    exe = os.path.join(tmp, "probe")
+    # the device code's symbol is the only one left open
+    r = subprocess.run([CLANG, "-no-pie", "-Wl,--unresolved-symbols=ignore-all"] + objs +
+                       ["-o", exe], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-4000:]
+
+    def run(calls):
+        r = subprocess.run([exe], input="\n".join(calls) + "\n", capture_output=True, text=True,
+                           timeout=60)
+        assert r.returncode == 0, r.stderr[-4000:]
+        parts = r.stdout.split("end\n")
+        assert len(parts) == len(calls) + 1 and parts[-1] == ""
+        return [p.splitlines() for p in parts[:-1]]
+
+    return run
+
+
+def test_band_eig_lds_limits_hold_on_every_device(launches):
+    """A kernel's dynamic LDS limit is a device's own: a second device gets
+    every launch the first one gets."""
+    calls = ["band %d %d %d" % c for c in ((900, 8, 10), (1448, 8, 10), (1000, 16, 16),
+                                           (3000, 4, 16), (2600, 10, 4), (9000, 12, 4))]
+    out = launches(calls + ["device 1"] + calls)
+    first, second = out[:len(calls)], out[len(calls) + 1:]
+    assert all(len(o) > 4 for o in first)
+    big = [l for o in first for l in o if int(l.split()[3]) > 65536]
+    assert len(big) >= 6
+    for call, a, b in zip(calls, first, second):
+        assert not any("refused" in l or l.startswith("error") for l in a + b), (call, a, b)
+        assert a == b

@@ -1055,9 +1055,20 @@ __device__ __forceinline__ void bwd_end(const double *L, double *X, int dir, int
   }
 }
 
+// dynamic LDS of the inverse iteration: factors and vector, or vectors
+constexpr size_t kInvLds = 158 * 1024;
+
+// Doubles of LDS of k_invit_two without and with room for the stages of the
+// factorisation's two sweeps.  Matrices too long for that have them where the
+// vector goes later (with kd = 8, k = 32, N = 1920 left to k_invit_reg 12.3 ms,
+// so 9.3); the others keep them apart, as the vector is then set up first (0.5 %).
 template <int KD>
-constexpr int invit_two_extra() {
-  return KD * KD + 2 * KD + 8 + 2 * BandStage<KD>::E;
+__host__ __device__ constexpr size_t invit_two_doubles(int N) {
+  return (size_t)N * (KD + 2) + KD * KD + 2 * KD + 8;
+}
+template <int KD>
+__host__ __device__ constexpr bool invit_two_apart(int N) {
+  return (invit_two_doubles<KD>(N) + 2 * BandStage<KD>::E) * sizeof(double) <= kInvLds;
 }
 
 // Inverse iteration (as k_invit_reg) with one workgroup per target and the
@@ -1075,7 +1086,8 @@ __global__ __launch_bounds__(128) void k_invit_two(const double *__restrict__ T,
                                                    double *X, int niter) {
   extern __shared__ double smem_inv[];
   double *L = smem_inv, *Dinv = L + (size_t)N * KD, *x = Dinv + N;
-  double *ex = x + N, *eq = ex + KD * KD, *en = eq + 2 * KD, *buf = en + 8;
+  constexpr int E = BandStage<KD>::E;
+  double *ex = x + N, *eq = ex + KD * KD, *en = eq + 2 * KD, *buf = invit_two_apart<KD>(N) ? en + 8 : x;
   const int t = threadIdx.x, lane = t & 63, up = __builtin_amdgcn_readfirstlane(t >> 6);
   const int tg = blockIdx.x, k = B.k;
   double lo, hi;
@@ -1086,21 +1098,26 @@ __global__ __launch_bounds__(128) void k_invit_two(const double *__restrict__ T,
   }
   if (tg >= k) return;
   const double theta = 0.5 * (lo + hi);
-  for (int i = t; i < N; i += 128)
-    x[i] = hash_unit((uint32_t)(i * 40503u + tg * 2654435761u + 7u));
+  auto start_vector = [&](int first, int step) {
+    for (int i = first; i < N; i += step)
+      x[i] = hash_unit((uint32_t)(i * 40503u + tg * 2654435761u + 7u));
+  };
+  if (invit_two_apart<KD>(N)) start_vector(t, 128);
   const Split sp = split_rows(N, KD);
   const int dir = up ? -1 : 1, m = up ? sp.m2 : sp.m1, e0 = up ? N - 1 : 0;
   double *Le = L + (size_t)e0 * KD, *De = Dinv + e0, *xe = x + e0;
   {
     double R[KD + 1];
     lane_sweep<KD>(up ? Tr : T, N, m, up ? 0 : sp.pad, theta, pivmin, R, Le, De, dir,
-                   buf + up * BandStage<KD>::E, lane);
+                   buf + up * E, lane);
     if (up && lane < KD) {
 #pragma unroll
       for (int j = 0; j < KD; ++j) ex[lane * KD + j] = R[j];
     }
     __syncthreads();
-    if (!up) {
+    if (up) {
+      if (!invit_two_apart<KD>(N)) start_vector(lane, 64);
+    } else {
       // both windows hold T - theta I of the middle, so it is taken out once
       if (lane < KD) {
 #pragma unroll
@@ -1556,9 +1573,7 @@ constexpr int kShiftsLds = 2048;
 constexpr double kNarrow = 2e12;
 constexpr int kInvIters = 2;
 constexpr double kPivmin = 1e-290, kInvPivmin = 1e-200;
-// dynamic LDS: vectors or factors of the inverse iteration; the Rayleigh-Ritz
-// basis beside its 42 KB of static LDS
-constexpr size_t kInvLds = 158 * 1024;
+// dynamic LDS of the Rayleigh-Ritz basis beside its 42 KB of static LDS
 constexpr size_t kRrLds = 118 * 1024;
 
 bool reg_bandwidth(int kd) {
@@ -1578,7 +1593,8 @@ template <int KD>
 void invit_reg_launch(const double *band, const double *rev, int N, const Bisect &B, int rounds,
                       double *brk, double *Lscr, double *Dscr, double *X, hipStream_t s) {
   const int k = B.k;
-  const size_t two = ((size_t)N * (KD + 2) + invit_two_extra<KD>()) * sizeof(double);
+  const size_t two =
+      (invit_two_doubles<KD>(N) + (invit_two_apart<KD>(N) ? 2 * BandStage<KD>::E : 0)) * sizeof(double);
   if (N >= KD && two <= kInvLds) {
     allow_lds(&k_invit_two<KD>, kInvLds);
     hipLaunchKernelGGL(k_invit_two<KD>, dim3(k + 1), dim3(128), two, s, band, rev, N, B, rounds,

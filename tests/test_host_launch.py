@@ -63,3 +63,11 @@ def test_band_eig_lds_limits_hold_on_every_device(launches):
     for call, a, b in zip(calls, first, second):
         assert not any("refused" in l or l.startswith("error") for l in a + b), (call, a, b)
         assert a == b
+
+
+def test_band_eig_factors_in_lds(launches):
+    """Up to 150 KB of factors and vector a target's inverse iteration keeps
+    them in LDS, one workgroup a target."""
+    calls = ["band %d %d 10" % (19200 // (kd + 2), kd) for kd in (1, 2, 4, 8, 10)]
+    for call, out in zip(calls, launches(calls)):
+        assert any(l.startswith("k_invit_two<") and l.split()[1] == "11" for l in out), (call, out)

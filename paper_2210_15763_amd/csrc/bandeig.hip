@@ -1589,6 +1589,19 @@ void allow_lds(K *kernel, size_t bytes) {
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
 }
 
+// LDS bytes and launch of k_invit: a 64-lane workgroup a target.
+size_t invit_bytes(int N, int kd) {
+  return (size_t)((kd + 1) * (kd + 1) + kChunk * (kd + 1) + N) * sizeof(double);
+}
+constexpr size_t kInvitLds = 150 * 1024;
+void invit_launch(const double *band, int N, int kd, const double *brk, int k, double *Lscr,
+                  double *Dscr, double *X, hipStream_t s) {
+  allow_lds(&k_invit, kInvitLds);
+  hipLaunchKernelGGL(k_invit, dim3(k), dim3(64), invit_bytes(N, kd), s, band, N, kd, brk, k,
+                     kInvPivmin, Lscr, Dscr, X, kInvIters);
+  check_launch("k_invit");
+}
+
 template <int KD>
 void invit_reg_launch(const double *band, const double *rev, int N, const Bisect &B, int rounds,
                       double *brk, double *Lscr, double *Dscr, double *X, hipStream_t s) {
@@ -1604,6 +1617,13 @@ void invit_reg_launch(const double *band, const double *rev, int N, const Bisect
   }
   hipLaunchKernelGGL(k_final_brackets, dim3(k + 1), dim3(128), 0, s, B, rounds, brk);
   check_launch("k_final_brackets");
+  // At 16 a lane's window and block of multipliers overflow the registers, and a
+  // workgroup a target is faster (us, k = 4 / 32: N = 1136 2130 / 2150 against
+  // 4260 / 6000, N = 3200 6030 / 6150 against 11820 / 21070).
+  if (KD == 16 && invit_bytes(N, KD) <= kInvitLds) {
+    invit_launch(band, N, KD, brk, k, Lscr, Dscr, X, s);
+    return;
+  }
   const size_t xbytes = (size_t)N * k * sizeof(double);
   if (xbytes <= kInvLds) {
     allow_lds(&k_invit_reg<KD, true>, kInvLds);
@@ -1697,12 +1717,9 @@ void band_eigensolve(const double *band, int N, int kd, int k, void *ws, const B
       check_launch("k_bisect_update");
       std::swap(sh_a, sh_b);
     }
-    const size_t smem = (size_t)((kd + 1) * (kd + 1) + kChunk * (kd + 1) + N) * sizeof(double);
-    BBL_REQUIRE(smem <= 150 * 1024, "band eigensolve: band matrix too large for LDS staging");
-    allow_lds(&k_invit, 150 * 1024);
-    hipLaunchKernelGGL(k_invit, dim3(k), dim3(64), smem, s, band, N, kd, brk, k, kInvPivmin, Lscr,
-                       Dscr, X, kInvIters);
-    check_launch("k_invit");
+    BBL_REQUIRE(invit_bytes(N, kd) <= kInvitLds,
+                "band eigensolve: band matrix too large for LDS staging");
+    invit_launch(band, N, kd, brk, k, Lscr, Dscr, X, s);
   }
   // Rayleigh-Ritz: Cholesky QR on matrix cores up to 16 pairs, else Gram-Schmidt
   if (k <= kRrMax) {

@@ -71,3 +71,13 @@ def test_band_eig_factors_in_lds(launches):
     calls = ["band %d %d 10" % (19200 // (kd + 2), kd) for kd in (1, 2, 4, 8, 10)]
     for call, out in zip(calls, launches(calls)):
         assert any(l.startswith("k_invit_two<") and l.split()[1] == "11" for l in out), (call, out)
+
+
+def test_band_eig_wide_bands_beyond_lds(launches):
+    """At bandwidth 16 with factors beyond LDS a target's inverse iteration has
+    a workgroup (k_invit), as at the bandwidths without a register window."""
+    calls = ["band %d %d %d" % c for c in ((1136, 16, 4), (1136, 16, 32), (8192, 16, 16),
+                                           (15, 16, 5), (900, 12, 5))]
+    for call, out in zip(calls, launches(calls)):
+        k = call.split()[-1]
+        assert any(l.split()[:2] == ["k_invit", k] for l in out), (call, out)

@@ -110,10 +110,17 @@ __device__ __forceinline__ double group_lane(double v, int e) {
 // the lookups of one lane that reads the row in E pieces.
 // Narrower rows, and rows that would split into pieces off 8 bytes (10
 // floats: 516 against 487 us, below), keep one lane.
+constexpr int entry_lanes(int elem, int b) {
+  return elem * b >= 64 && b % 4 == 0 ? 4 : elem * b >= 32 && elem * b % 16 == 0 ? 2 : 1;
+}
 template <typename XT, int B>
 constexpr int entry_lanes() {
-  constexpr int bytes = (int)sizeof(XT) * B;
-  return bytes >= 64 && B % 4 == 0 ? 4 : bytes >= 32 && bytes % 16 == 0 ? 2 : 1;
+  return entry_lanes((int)sizeof(XT), B);
+}
+// widths with a compiled kernel
+constexpr bool compiled_width(int b) {
+  return (b >= 1 && b <= 6) || b == 8 || b == 10 || b == 12 || b == 16 || b == 20 || b == 24 ||
+         b == 32;
 }
 
 // U * LPR entries of a row from offset q on: a lane loads U entries, and every
@@ -485,12 +492,27 @@ __global__ __launch_bounds__(256) void k_residual(int64_t n, const int64_t *__re
 // matrices (n = 2e6, 200 nonzeros a row), 32 from 400 nonzeros a row on.
 // Short matrices leave the chip idle and are bound by the chain of steps of a
 // row, which more lanes shorten: 8 floats wide, 121 nonzeros a row, 16 / 32 /
-// 64 lanes: n = 1000 8.4 / 5.9 / 4.3 us, 3000 10.0 / 6.8 / 5.0, 8000 6.0 / 5.6
-// / 6.4, 20,000 9.4 / 9.5 / 9.9 (41 a row: 5.7 / 6.4 / 7.8).
-int pick_lpr(const bbl_csr &H) {
-  if (H.n <= 4096) return 64;
+// 64 lanes: n = 1000 8.4 / 5.9 / 4.3 us, 3000 10.0 / 6.8 / 5.0 (41 a row,
+// 20,000 rows: 5.7 / 6.4 / 7.8).  Where the gathers take over, fewer are better
+// again (us a call): 10 floats, 500 a row, n = 4000 8.5 / 8.7 / 9.9, but rows
+// that several lanes gather still gain (20 floats 16.5 / 15.6 / 14.5); n = 6000,
+// 300 a row, 8 floats 7.9 / 7.1 / 8.1; n = 8000 9.0 / 9.6 / 11.0.
+// The generic kernel reduces 32 columns whatever its width, so that more lanes
+// pay for themselves only on the shortest matrices and on long rows (7 doubles,
+// 5 / 121 a row, n = 1000 5.9 / 6.6 / 7.1 and 11.8 / 9.2 / 8.3, n = 2000 6.0 /
+// 6.5 / 10.8 and 12.8 / 9.9 / 13.4, n = 4000 5.9 / 9.5 / 18.7 and 14.1 / 15.6 /
+// 23.7; 300 a row, 7 floats, n = 2000 20 / 13 / 11, n = 4000 22 / 17 / 21,
+// n = 6000 29 / 25 / 35, 7 doubles 32 / 34 / 42).
+int pick_lpr(const bbl_csr &H, int elem, int nvec, bool compiled, int lanes) {
   const double z = H.n > 0 ? (double)H.nnz / (double)H.n : 0.0;
-  return z < 400.0 && H.n > 8192 ? 16 : 32;
+  const int by_row = z < 400.0 ? 16 : 32;
+  if (compiled) {
+    if (H.n <= 2560 || (H.n <= 4096 && (lanes > 1 || H.nnz <= 600000))) return 64;
+    return H.n <= 6144 ? 32 : by_row;
+  }
+  if (H.n <= 1024) return 64;
+  if (H.n <= 3072 && (H.n <= 2048 || z >= 64.0)) return elem == 4 && z >= 200.0 ? 64 : 32;
+  return H.n <= 6144 && nvec <= 16 && z >= (elem == 4 ? 200.0 : 350.0) ? 32 : by_row;
 }
 
 template <typename VT, typename XT, typename AT, typename YT, int LPR>
@@ -539,7 +561,8 @@ void spmm_dispatch_b(const bbl_csr &H, const XT *X, YT *Y, int nvec, hipStream_t
 
 template <typename VT, typename XT, typename AT, typename YT>
 void spmm_dispatch(const bbl_csr &H, const XT *X, YT *Y, int nvec, hipStream_t s) {
-  switch (pick_lpr(H)) {
+  switch (pick_lpr(H, (int)sizeof(XT), nvec, compiled_width(nvec),
+                   entry_lanes((int)sizeof(XT), nvec))) {
     case 16: spmm_dispatch_b<VT, XT, AT, YT, 16>(H, X, Y, nvec, s); break;
     case 32: spmm_dispatch_b<VT, XT, AT, YT, 32>(H, X, Y, nvec, s); break;
     default: spmm_dispatch_b<VT, XT, AT, YT, 64>(H, X, Y, nvec, s); break;
@@ -2072,8 +2095,10 @@ int residual_t(const bbl_csr &H, const double *X, const double *theta, double *p
 
 int launch_residual_spmm(const bbl_csr &H, const double *X, int nvec, const double *theta,
                          double *partial, int max_partials, hipStream_t s) {
-  const int lpr = pick_lpr(H);
-  if (max_partials >= 8) {
+  const bool compiled =
+      max_partials >= 8 && (nvec == 4 || nvec == 8 || nvec == 10 || nvec == 16);
+  const int lpr = pick_lpr(H, 8, nvec, compiled, 1);
+  if (compiled) {
     switch (nvec) {
       case 4: return residual_t<4>(H, X, theta, partial, max_partials, lpr, s);
       case 8: return residual_t<8>(H, X, theta, partial, max_partials, lpr, s);

@@ -81,3 +81,28 @@ def test_band_eig_wide_bands_beyond_lds(launches):
     for call, out in zip(calls, launches(calls)):
         k = call.split()[-1]
         assert any(l.split()[:2] == ["k_invit", k] for l in out), (call, out)
+
+
+F32, F64 = 1, 2
+
+
+def spmm_kernel(launches, calls):
+    """Name of the one kernel of each call (n, nonzeros a row, type, width)."""
+    out = launches(["spmm %d %d %d %d %d" % (n, n * z, dt, b, dt) for n, z, dt, b in calls])
+    assert all(len(o) == 1 for o in out)
+    return [o[0].split()[0] for o in out]
+
+
+def test_spmm_lanes_of_short_matrices(launches):
+    """Widths without a compiled kernel keep 16 lanes a row on matrices past
+    3072 rows (their reduction covers 32 columns), compiled ones up to 64."""
+    generic = [(n, z, dt, b) for n in (3073, 4000, 6000, 8192) for z in (5, 31, 121)
+               for dt in (F32, F64) for b in (7, 9, 13, 28, 31)]
+    for call, k in zip(generic, spmm_kernel(launches, generic)):
+        assert k.startswith("k_spmm_generic<") and k.endswith(",16>"), (call, k)
+    rest = [((1000, 61, F32, 7), 64), ((2000, 61, F64, 13), 32),
+            ((3000, 31, F64, 13), 16), ((3000, 121, F64, 13), 32), ((6000, 300, F64, 7), 16), ((1000, 121, F32, 8), 64),
+            ((4000, 121, F64, 4), 64), ((4000, 300, F32, 10), 32), ((6000, 121, F32, 8), 32),
+            ((8000, 300, F32, 10), 16), ((8000, 300, F32, 12), 16), ((9000, 450, F64, 8), 32)]
+    for (call, lanes), k in zip(rest, spmm_kernel(launches, [c for c, _ in rest])):
+        assert k.endswith(",%d>" % lanes), (call, k)

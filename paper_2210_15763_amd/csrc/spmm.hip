@@ -515,6 +515,27 @@ int pick_lpr(const bbl_csr &H, int elem, int nvec, bool compiled, int lanes) {
   return H.n <= 6144 && nvec <= 16 && z >= (elem == 4 ? 200.0 : 350.0) ? 32 : by_row;
 }
 
+// Whether groups of lanes gather an entry's row together (k_spmm_split) or a
+// lane takes whole rows (k_spmm).  The group's wide loads pay off from about 40
+// entries a row on, where a lane has several in flight, on very short rows,
+// where most lanes of k_spmm idle, and while V stays in the caches; otherwise
+// k_spmm, with more waves resident, hides the latency of its one or two steps
+// better.  us of the group against k_spmm at 32 bytes a row of V, n = 2e6 (4e5; 1e5;
+// 3e4): 9 entries a row 193 / 174 (34 / 35; 8.1 / 10.6), 17 312 / 259 (52 / 46;
+// 14.1 / 12.9; 5.3 / 6.0), 33 472 / 404 (73 / 66; 21.0 / 19.1), 41 489 / 529 (75 /
+// 81; 21.7 / 23.5); at 64 bytes 13 395 / 335 (64 / 68; 18.0 / 20.2), 17 473 / 380
+// (76 / 70; 21.2 / 21.2; 6.3 / 8.5), 25 501 / 503 (77 / 81; 22.0 / 24.5); at 80
+// bytes 33 869 / 836 (134 / 129; 36.2 / 36.3), 41 964 / 1061.  From 96 bytes on
+// the group is faster at any length (17 entries 600 / 689).
+template <typename XT, int B>
+bool group_gathers(const bbl_csr &H) {
+  constexpr int bytes = (int)sizeof(XT) * B;
+  const double z = (double)H.nnz / (double)H.n, v = (double)H.n * bytes;
+  if (bytes < 64)
+    return v <= 2e6 || z < (v > 32e6 ? 8.0 : v > 8e6 ? 11.0 : 15.0) || z >= 38.0;
+  return v <= 16e6 || z < (v > 32e6 ? 11.0 : 15.0) || z >= (bytes == 64 ? 24.0 : 38.0);
+}
+
 template <typename VT, typename XT, typename AT, typename YT, int LPR>
 void spmm_dispatch_b(const bbl_csr &H, const XT *X, YT *Y, int nvec, hipStream_t s) {
   const int rows_per_wg = (256 / kWave) * (kWave / LPR);
@@ -527,14 +548,19 @@ void spmm_dispatch_b(const bbl_csr &H, const XT *X, YT *Y, int nvec, hipStream_t
     const int64_t grid = ceil_div(ceil_div(nr, rows_per_wg), kXcds) * kXcds;
     const int64_t *rp = H.row_ptr + r0;
     YT *Yc = Y + r0 * nvec;
-#define BBL_SPMM_CASE(BV)                                                                       \
-  case BV:                                                                                      \
-    if constexpr (entry_lanes<XT, BV>() > 1)                                                    \
-      hipLaunchKernelGGL((k_spmm_split<VT, XT, AT, YT, BV, LPR>), dim3(grid), dim3(256), 0, s,  \
-                         nr, rp, H.col, val, X, Yc);                                            \
-    else                                                                                        \
-      hipLaunchKernelGGL((k_spmm<VT, XT, AT, YT, BV, LPR>), dim3(grid), dim3(256), 0, s, nr, rp, \
-                         H.col, val, X, Yc);                                                    \
+#define BBL_SPMM_KERNEL(K, BV)                                                               \
+  hipLaunchKernelGGL((K<VT, XT, AT, YT, BV, LPR>), dim3(grid), dim3(256), 0, s, nr, rp, H.col, \
+                     val, X, Yc)
+#define BBL_SPMM_CASE(BV)                                                                    \
+  case BV:                                                                                   \
+    if constexpr (entry_lanes<XT, BV>() == 1) {                                              \
+      BBL_SPMM_KERNEL(k_spmm, BV);                                                           \
+    } else if constexpr (LPR > 16 || sizeof(XT) * BV >= 96) {                                \
+      BBL_SPMM_KERNEL(k_spmm_split, BV);                                                     \
+    } else {                                                                                 \
+      if (group_gathers<XT, BV>(H)) BBL_SPMM_KERNEL(k_spmm_split, BV);                       \
+      else BBL_SPMM_KERNEL(k_spmm, BV);                                                      \
+    }                                                                                        \
     break;
     switch (nvec) {
       BBL_SPMM_CASE(1)
@@ -555,6 +581,7 @@ void spmm_dispatch_b(const bbl_csr &H, const XT *X, YT *Y, int nvec, hipStream_t
                            rp, H.col, val, X, Yc, nvec);
     }
 #undef BBL_SPMM_CASE
+#undef BBL_SPMM_KERNEL
     check_launch("k_spmm");
   }
 }

@@ -106,3 +106,22 @@ def test_spmm_lanes_of_short_matrices(launches):
             ((8000, 300, F32, 10), 16), ((8000, 300, F32, 12), 16), ((9000, 450, F64, 8), 32)]
     for (call, lanes), k in zip(rest, spmm_kernel(launches, [c for c, _ in rest])):
         assert k.endswith(",%d>" % lanes), (call, k)
+
+
+def test_spmm_of_short_rows(launches):
+    """Rows of V of 32 to 80 bytes: a lane takes whole rows where a row of the
+    matrix has some 10 to 40 entries and V outgrows the caches, groups share them elsewhere."""
+    own = [(n, z, dt, b) for n in (400000, 2000000) for z in (17, 22)
+           for dt, b in ((F32, 8), (F32, 12), (F32, 16), (F32, 20), (F64, 4), (F64, 8), (F64, 10))]
+    own += [(100000, 31, F32, 8), (400000, 37, F64, 4), (2000000, 9, F32, 12), (2000000, 13, F32, 16),
+            (400000, 33, F64, 10), (400000, 61, F32, 10), (400000, 61, F64, 3)]
+    for call, k in zip(own, spmm_kernel(launches, own)):
+        assert k.startswith("k_spmm<"), (call, k)
+    shared = [(n, z, dt, b) for n in (9000, 400000, 2000000) for z in (5, 41, 211, 420)
+              for dt, b in ((F32, 8), (F32, 16), (F64, 4), (F64, 10))]
+    shared += [(n, z, dt, b) for n in (9000, 2000000) for z in (5, 17, 33, 61)
+               for dt, b in ((F32, 24), (F32, 32), (F64, 12), (F64, 16))]
+    shared += [(400000, 9, F32, 8), (400000, 31, F64, 8), (4000, 17, F32, 8), (30000, 17, F32, 8),
+               (100000, 17, F64, 8), (100000, 33, F64, 10)]
+    for call, k in zip(shared, spmm_kernel(launches, shared)):
+        assert k.startswith("k_spmm_split<"), (call, k)

@@ -36,11 +36,9 @@ __device__ __forceinline__ d4 mfma16(double a, double b, d4 c) {
 template <typename T>
 __device__ __forceinline__ double ld(const T *p) { return (double)*p; }
 
-constexpr int kGramRowsWgs = 2048;        // workgroups of k_gram_rows
-// up to here a gram keeps to 64 row chunks where those already fill the chip:
-// the reduction of the partials then takes one stage instead of two (about
-// 3 us of the 10-20 us of such a gram)
-constexpr int64_t kGramShort = 65536;
+// workgroups of k_gram_rows; at two blocks a lane three fit a CU, and a few more
+// than fit the chip at once leave a second round nearly empty
+constexpr int kGramRowsWgs = 2048, kGramRowsResident = 768;
 constexpr int kTilesPerWG = 8;   // 16-column tiles of X handled by one gram WG
 #ifndef BBL_GRAM_WAVE_TARGET
 #define BBL_GRAM_WAVE_TARGET 6144
@@ -915,7 +913,7 @@ __global__ __launch_bounds__(64) void k_gram_v(int64_t n, const XT *__restrict__
   }
 }
 
-// Gram of narrow blocks (B = 4 in float32, 4, 8 or 10 in float64) against all
+// Gram of narrow blocks (B = 4, or 10 in float64) against all
 // of Y's B columns.  A wave reads RG rows of NX x NBW blocks at a time, each
 // lane one 16-byte piece of a block row, so that every load instruction takes
 // whole 128-byte lines whatever the number of blocks, and keeps the products of
@@ -927,7 +925,7 @@ __global__ __launch_bounds__(64) void k_gram_v(int64_t n, const XT *__restrict__
 // workgroup ids congruent mod 8: one XCD, whose L2 then serves their rereads of
 // Y.  Bound by the reads of X and of Y (FP64; with few blocks Y is much of
 // them): n = 2e6, two FP32 blocks of 4 49 us (290 in a kernel with a column
-// group of 64 a wave, mostly empty), 8 FP64 blocks of 8 280 (419) = 4.1 TB/s.
+// group of 64 a wave, mostly empty), 4 FP64 blocks of 4 86 (176).
 template <typename XT, int B>
 struct GramRows {
   static constexpr int CPL = 16 / (int)sizeof(XT);       // columns of a lane's piece
@@ -1332,12 +1330,14 @@ int gram_rows(int64_t n, const XT *X, int nblk, int64_t xstride, const YT *Y, do
               int max_partials, const int *when, hipStream_t s) {
   using G = GramRows<XT, B>;
   const int gy = (int)ceil_div(nblk, NX * G::NBW);
-  // about kGramRowsWgs workgroups, of at least two rounds of rows each; where
-  // 64 row chunks already give every CU a workgroup, no more: the partials
-  // then need one stage of reduction
-  int64_t gx = std::max<int64_t>(1, kGramRowsWgs / gy);
+  // of at least two rounds of rows each.  Two blocks a lane: one round of
+  // workgroups, gx (which the grid rounds up to a multiple of 8) rounded down to
+  // one (10-wide FP64 blocks, 768 / 640 / 2048 workgroups: n = 65,000, 45 blocks 48 /
+  // 50 / 60 us, n = 400,000 310 / 353 / 353; 784 instead of 672 at n = 65,000, 80
+  // blocks 154 / 112 / 118)
+  int64_t gx = NX > 1 ? std::max<int64_t>(8, kGramRowsResident / gy / 8 * 8)
+                      : std::max<int64_t>(1, kGramRowsWgs / gy);
   gx = std::min(gx, ceil_div(n, 8 * 4 * G::RG));
-  if (n <= kGramShort && gy >= 4) gx = std::min<int64_t>(gx, 64);
   gx = std::max<int64_t>(1, std::min<int64_t>(gx, max_partials));
   const int64_t chunk = ceil_div(ceil_div(n, gx), 4 * G::RG) * 4 * G::RG;
   gx = ceil_div(n, chunk);
@@ -1366,7 +1366,15 @@ int gram_quads(int64_t n, const XT *X, int nblk, int64_t xstride, const YT *Y, d
   const int U = small ? (sizeof(XT) == 8 ? kGramSmallU / 2 : kGramSmallU) : 2;
   const int64_t rows = small ? WR * kGramSmallChunk : 256;  // of a workgroup, at least
   gx = std::max<int64_t>(1, std::min<int64_t>(gx, ceil_div(n, rows)));
-  if (small && WR > 1 && n <= kGramShort) gx = std::min<int64_t>(gx, 64);
+  // 64 row chunks where they give every CU a workgroup and few rows make them
+  // short: the partials then need one stage of reduction (8-wide FP64 blocks, n =
+  // 65,000, 32 / 150 blocks 25 / 122 us against 28 / 131, 4-wide FP32 ones, n =
+  // 40,000, 120 blocks 25 against 27; with fewer blocks or of 20,000 rows the chip
+  // idles: 9 FP64 blocks 21 against 15, n = 20,000, 45 blocks 18 against 16, 20 FP32
+  // blocks of 65,000 rows 30 against 14)
+  if (WR > 1 && small && n > 24576 && gy >= (sizeof(XT) == 8 ? 4 : 8) &&
+      n <= (sizeof(XT) == 8 || gy >= 12 ? 65536 : 49152))
+    gx = std::min<int64_t>(gx, 64);
   gx = std::min<int64_t>(gx, std::max(1, max_partials));
   const int64_t step = 4 * U * (small ? WR : 1);
   const int64_t chunk = ceil_div(ceil_div(n, gx), step) * step;
@@ -1451,23 +1459,21 @@ int gram_typed(int64_t n, const XT *X, int bx, int nblk, int64_t xstride, const 
     check_launch("k_gram_mfma10");
     return (int)gx;
   }
-  // 4- and 8-wide blocks.  Up to 8 of them k_gram_rows, whose lanes spread over
-  // the rows (k_gram_quads' group of 64 columns would be partly empty: n = 4e5,
-  // 8 FP64 blocks of 8, 57 us against 69 of k_gram_v and 8 FP32 blocks of 4,
-  // 28 against 67), except FP32 blocks of 8, two to a 64-byte line, where
-  // k_gram_quads has 41 us.  More of them k_gram_quads (n = 4e5, 45 blocks:
-  // FP64 by 8 228 us against 271 of k_gram_v, FP32 by 4 79 against 119), but
-  // k_gram_v for FP64 blocks of 4 (20 blocks 52 us against 64, 150 339
-  // against 361).
-  if (ny == bx && nblk >= 2 && (bx == 4 || bx == 8)) {
-    if (!(f32 && bx == 8) && nblk <= 8) {
-      if (bx == 4)
-        return gram_rows<XT, YT, 4, 1>(n, X, nblk, xstride, Y, partial, max_partials, when, s);
-      if constexpr (!f32)
-        return gram_rows<XT, YT, 8, 1>(n, X, nblk, xstride, Y, partial, max_partials, when, s);
-    }
-    if (bx == 8)
-      return gram_quads<XT, YT, 8>(n, X, nblk, xstride, Y, partial, max_partials, when, s);
+  // 4- and 8-wide blocks: 8-wide k_gram_quads (FP64, n = 2e6, 2 / 8 blocks 100 /
+  // 224 us against 228 / 282 of k_gram_rows and 378 / 420 of k_gram_v; n = 4e5, 45
+  // 228 against 271 of k_gram_v).  4-wide blocks, up to 8 of them: k_gram_rows,
+  // whose lanes spread over the rows (a group of 64 columns would be partly
+  // empty: n = 2e6, 4 FP64 blocks 86 us against 94 and 176 of k_gram_v).  More of
+  // them: FP32 k_gram_quads (n = 4e5, 45 blocks 79 against 119 of k_gram_v), FP64
+  // k_gram_v, as neither is the faster throughout (n = 4e5, 20 / 45 / 80 / 150
+  // blocks 52 / 125 / 198 / 362 us against 64 / 119 / 192 / 362; n = 2e6, 9 / 16 / 20
+  // 200 / 228 / 268 against 129 / 208 / 296; n = 20,000, 45 / 150 16.3 / 24.0 against
+  // 12.3 / 25.5).
+  if (ny == bx && nblk >= 2 && bx == 8)
+    return gram_quads<XT, YT, 8>(n, X, nblk, xstride, Y, partial, max_partials, when, s);
+  if (ny == bx && nblk >= 2 && bx == 4) {
+    if (nblk <= 8)
+      return gram_rows<XT, YT, 4, 1>(n, X, nblk, xstride, Y, partial, max_partials, when, s);
     if constexpr (f32)
       return gram_quads<XT, YT, 4>(n, X, nblk, xstride, Y, partial, max_partials, when, s);
     else

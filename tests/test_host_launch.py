@@ -125,3 +125,29 @@ def test_spmm_of_short_rows(launches):
                (100000, 17, F64, 8), (100000, 33, F64, 10)]
     for call, k in zip(shared, spmm_kernel(launches, shared)):
         assert k.startswith("k_spmm_split<"), (call, k)
+
+
+def test_gram_grids(launches):
+    """Kernels and grids of the products of narrow blocks: 8-wide FP64 blocks
+    of any number on matrix cores; no short matrix with few blocks held to 64
+    row chunks; more than six 10-wide FP64 blocks on as many workgroups as
+    the chip holds at once (768)."""
+    def one(n, dt, b, nblk):
+        out = launches(["gram %d %d %d %d" % (n, dt, b, nblk)])[0]
+        assert len(out) == 2 and out[1].startswith("parts ")
+        name, grid = out[0].split()[:2]
+        return name.split("<")[0], int(grid), int(out[1].split()[1])
+
+    for n in (500, 65000, 130000, 2000000):
+        for nblk in (2, 3, 8, 9, 45):
+            assert one(n, F64, 8, nblk)[0] == "k_gram_quads"
+    for dt, b, n, nblk in ((F32, 4, 65000, 20), (F32, 4, 40000, 45), (F64, 8, 65000, 9),
+                           (F64, 8, 20000, 45)):
+        assert one(n, dt, b, nblk)[2] > 64
+    assert one(65000, F64, 8, 45)[2] <= 64
+    for n in (65000, 400000):
+        for nblk in (7, 16, 20, 45, 80, 120, 150, 180):
+            name, grid, _ = one(n, F64, 10, nblk)
+            assert name == "k_gram_rows" and 640 < grid <= 768, (n, nblk, grid)
+    for dt, b in ((F32, 4), (F64, 4)):
+        assert one(400000, dt, b, 4)[0] == "k_gram_rows"

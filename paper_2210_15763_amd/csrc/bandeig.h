@@ -5,8 +5,11 @@
 
 namespace bbl {
 
+// rev: the reversed band of the two-sided factorisation, N (kd + 1) doubles.  It
+// lies over the factors Lscr and Dscr (k N (kd + 1) doubles together; with one
+// target it takes all of both), which only kernels that do not read it write.
 struct BandEigLayout {
-  size_t gersh, shifts_a, shifts_b, counts, brk, Lscr, Dscr, X, TX, flag, bytes;
+  size_t gersh, shifts_a, shifts_b, counts, brk, rev, Lscr, Dscr, X, TX, bytes;
 };
 
 // Workspace layout for N x N band matrices of half-bandwidth kd, k pairs.

@@ -1655,9 +1655,10 @@ BandEigLayout band_eig_layout(int N, int kd, int k) {
   L.brk = take(2 * NT * sizeof(double));
   L.Lscr = take((size_t)k * N * std::max(kd, 1) * sizeof(double));
   L.Dscr = take((size_t)k * N * sizeof(double));
+  L.rev = L.Lscr;
+  off = std::max(off, L.rev + align_up((size_t)N * (kd + 1) * sizeof(double)));
   L.X = take((size_t)N * k * sizeof(double));
   L.TX = take((size_t)N * k * sizeof(double));
-  L.flag = take(64);
   L.bytes = off;
   return L;
 }
@@ -1684,10 +1685,8 @@ void band_eigensolve(const double *band, int N, int kd, int k, void *ws, const B
   int rounds = 1;
   for (double f = nsh + 1.0; f < kNarrow; f *= SP + 1.0) ++rounds;
   if (regk) {
-    // the reversed band takes the place of the factors, which only the large
-    // sizes keep in memory, after their last use of it; the counts and the
-    // rounds' brackets that of the shift lists
-    double *rev = Lscr;
+    // the counts and the rounds' brackets take the place of the shift lists
+    double *rev = reinterpret_cast<double *>(base + L.rev);
     const int ng = std::min(kGershMax, (N + 127) / 128);
     double *bounds = sh_a + kShiftsReg / 2;  // past the brackets
     Bisect B{bounds, ng, sh_a, {counts, reinterpret_cast<int *>(sh_b)}, nsh, SP, k, N};

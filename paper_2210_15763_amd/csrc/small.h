@@ -234,7 +234,8 @@ struct Parts {
   const double *p = nullptr;
   int P = 0;
 };
-// one workgroup adds up this many doubles of partials (512 KB)
+// one workgroup adds up at most this many doubles of partials of a matrix
+// (512 KB; k_step_qr adds up two matrices)
 constexpr int64_t kPartsMax = 65536;
 
 // The small steps of a block on the fast path, b <= kWaveMat, one launch each:
